@@ -94,6 +94,31 @@ def test_cd_sample_matches_oracle(vocab, temperature, scale):
         assert all(np.isfinite(logits[r, t]) for t in toks)
 
 
+@pytest.mark.parametrize("n_rows,vocab", [(256, 4096), (257, 8191), (300, 16 * 4096), (300, 16 * 4096 + 1),
+                                          (5, 3 * 4096 + 1), (460, 151939)])
+def test_cd_sample_workgroup_sizes(n_rows, vocab):
+    # 16 waves per row up to 256 rows, beyond them 4 (up to 16 tiles) or 8, non-temporal loads past 256 MB
+    # of logits (460 rows of 151,939); tiles that end with the vocabulary, one token into the next tile, and rows that do not
+    # start 16-byte aligned.  The first and last rows are checked against the oracle.
+    g = torch.Generator(device="cuda")
+    g.manual_seed(vocab)
+    logits = torch.empty((n_rows, vocab), device="cuda").normal_(0.0, 4.0, generator=g)
+    rows = [0, 1, n_rows // 2, n_rows - 1]
+    host = logits[rows].cpu().numpy()
+    rng = np.random.default_rng(vocab)
+    potential = rng.integers(0, 5, size=n_rows)
+    potential[rows] = [3, 64, 1, 17]
+    import paper_2609_39334_amd as tkv
+    off = np.concatenate([[0], np.cumsum(potential)]).astype(np.int32)
+    u = rng.random(int(off[-1]), dtype=np.float32)
+    tok, cnt, ng = tkv.tkv_cd_sample(logits, 0.8, torch.from_numpy(off).cuda(), torch.from_numpy(u).cuda(), 64)
+    tok, cnt, ng = tok.cpu().numpy(), cnt.cpu().numpy(), ng.cpu().numpy()
+    assert [int(sum(cnt[off[r]:off[r] + ng[r]])) for r in range(n_rows)] == potential.tolist()
+    sub = np.concatenate([np.arange(off[r], off[r + 1]) for r in rows])
+    _check_rows(host, 0.8, potential[rows], np.concatenate([[0], np.cumsum(potential[rows])]).astype(np.int32), u[sub],
+                tok[sub], cnt[sub], ng[rows])
+
+
 def test_cd_sample_distribution():
     # 100 rows of the same 50-token distribution, 1024 draws each: chi-square against the probabilities
     from scipy.stats import chi2
