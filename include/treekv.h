@@ -356,6 +356,29 @@ int tkv_verify_noalloc(const tkv_plan* plan, const void* q, const void* k, const
 int tkv_kv_append(const tkv_shape* shape, const int32_t* d_dst, int32_t n_tok, const void* k_new, const void* v_new,
                   void* k, void* v, void* hip_stream);
 
+/* ======================================================================== decoder layer
+ * The elementwise steps between a decoder layer's matrix products, one pass over memory each: fp32
+ * arithmetic, bf16 results rounded to nearest even.  Tensors are contiguous device memory; enqueued on
+ * hip_stream.  EINVAL (sizes, NULL pointers, alignment), EHIP. */
+
+/* x[n_rows][hidden] fp32 += delta[n_rows][hidden] bf16 (nullable: no addition, x is not written), then
+ * h[n_rows][hidden] bf16 = x / sqrt(mean(x^2) + eps) * weight[hidden] (fp32). */
+int tkv_add_rmsnorm(int32_t n_rows, int32_t hidden, float eps, float* x, const void* delta, const float* weight,
+                    void* h, void* hip_stream);
+
+/* Rotate-half RoPE of new tokens' queries and keys, and their K/V append (tkv_kv_append):
+ *   qkv         [n_tok][hq + 2 hkv][d] bf16: each token's query, key and value heads
+ *   cosv, sinv  [n_tok][d / 2] fp32: of each token's rotation angles
+ *   d_dst       [n_tok] int32: pool slots; a token with a slot of -1 (or outside the pool) writes no K/V
+ *   q           [n_tok][hq][d] bf16: the rotated queries
+ *   k, v        the pool, [num_blocks][hkv][block_size][d] bf16, written at the slots (k rotated)
+ * Every field of shape is used (block_size 16, d in {64, 128}).  Tensors 16-byte aligned. */
+int tkv_rope_append(const tkv_shape* shape, int32_t n_tok, const void* qkv, const float* cosv, const float* sinv,
+                    const int32_t* d_dst, void* q, void* k, void* v, void* hip_stream);
+
+/* out[n_rows][inter] bf16 = SiLU(gu[:, :inter]) * gu[:, inter:], gu [n_rows][2 inter] bf16. */
+int tkv_swiglu(int32_t n_rows, int32_t inter, const void* gu, void* out, void* hip_stream);
+
 /* ======================================================================== CD branching sampler
  * On-demand branching of computation deduplication (Sec. 4.2): a sequence with potential size n
  * stands for n identical candidates; its one row of logits gives n independent draws from the

@@ -91,6 +91,9 @@ _SIG = {
     "tkv_verify": (ctypes.c_int, [_P, _P, _P, _P, _P, _P, _P]),
     "tkv_verify_noalloc": (ctypes.c_int, [_P, _P, _P, _P, _P, _P, _P]),
     "tkv_kv_append": (ctypes.c_int, [ctypes.POINTER(tkv_shape), _P, _I32, _P, _P, _P, _P, _P]),
+    "tkv_add_rmsnorm": (ctypes.c_int, [_I32, _I32, ctypes.c_float, _P, _P, _P, _P, _P]),
+    "tkv_rope_append": (ctypes.c_int, [ctypes.POINTER(tkv_shape), _I32, _P, _P, _P, _P, _P, _P, _P, _P]),
+    "tkv_swiglu": (ctypes.c_int, [_I32, _I32, _P, _P, _P]),
     "tkv_cd_sample": (ctypes.c_int, [_I32, _I32, ctypes.c_float, _I32, _P, _P, _P, _I32, _P, _P, _P, _P]),
     "tkv_search_create": (ctypes.c_int, [_I32, _I32, _I32, _I32, ctypes.POINTER(_P)]),
     "tkv_search_destroy": (None, [_P]),
@@ -409,6 +412,55 @@ def tkv_kv_append(dst: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, k
     shape = tkv_shape(0, hkv, d, bs, nb)
     _check(lib().tkv_kv_append(ctypes.byref(shape), dst.data_ptr(), n, k_new.data_ptr(), v_new.data_ptr(),
                                k.data_ptr(), v.data_ptr(), _stream(stream)))
+
+
+def _expect(fn: str, name: str, t: torch.Tensor, dtype, shape) -> None:
+    if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or not t.is_cuda:
+        raise ValueError(f"{fn}: {name} must be a contiguous {dtype} GPU tensor of shape {tuple(shape)}, got {t.dtype} "
+                         f"{tuple(t.shape)}")
+
+
+def tkv_add_rmsnorm(x: torch.Tensor, delta: Optional[torch.Tensor], weight: torch.Tensor, eps: float,
+                    stream=None) -> torch.Tensor:
+    """x [rows, hidden] fp32 += delta (bf16, or None) in place; returns RMSNorm(x) * weight in bf16."""
+    rows, hidden = x.shape
+    _expect("tkv_add_rmsnorm", "x", x, torch.float32, (rows, hidden))
+    _expect("tkv_add_rmsnorm", "weight", weight, torch.float32, (hidden,))
+    if delta is not None:
+        _expect("tkv_add_rmsnorm", "delta", delta, torch.bfloat16, (rows, hidden))
+    h = torch.empty((rows, hidden), dtype=torch.bfloat16, device=x.device)
+    _check(lib().tkv_add_rmsnorm(rows, hidden, float(eps), x.data_ptr(), None if delta is None else delta.data_ptr(),
+                                 weight.data_ptr(), h.data_ptr(), _stream(stream)))
+    return h
+
+
+def tkv_rope_append(qkv: torch.Tensor, cos: torch.Tensor, sin: torch.Tensor, dst: torch.Tensor, hq: int,
+                    k: torch.Tensor, v: torch.Tensor, stream=None) -> torch.Tensor:
+    """RoPE of qkv [n, (hq + 2 hkv) * d] bf16; writes k and v rows to the pool slots dst (int32, -1 = skip) and
+    returns the rotated queries [n, hq, d].  cos, sin: [n, d / 2] fp32; k, v: the pools."""
+    fn = "tkv_rope_append"
+    nb, hkv, bs, d = k.shape
+    n = int(dst.numel())
+    _expect(fn, "qkv", qkv, torch.bfloat16, (n, (hq + 2 * hkv) * d))
+    _expect(fn, "cos", cos, torch.float32, (n, d // 2))
+    _expect(fn, "sin", sin, torch.float32, (n, d // 2))
+    _expect(fn, "k", k, torch.bfloat16, k.shape)
+    _expect(fn, "v", v, torch.bfloat16, k.shape)
+    _expect(fn, "dst", dst, torch.int32, dst.shape)
+    q = torch.empty((n, hq, d), dtype=torch.bfloat16, device=qkv.device)
+    shape = tkv_shape(hq, hkv, d, bs, nb)
+    _check(lib().tkv_rope_append(ctypes.byref(shape), n, qkv.data_ptr(), cos.data_ptr(), sin.data_ptr(), dst.data_ptr(),
+                                 q.data_ptr(), k.data_ptr(), v.data_ptr(), _stream(stream)))
+    return q
+
+
+def tkv_swiglu(gu: torch.Tensor, stream=None) -> torch.Tensor:
+    """SiLU(gate) * up of gu [rows, 2 * inter] bf16 (gate first), in bf16."""
+    rows, two = gu.shape
+    _expect("tkv_swiglu", "gu", gu, torch.bfloat16, (rows, two - two % 2))
+    out = torch.empty((rows, two // 2), dtype=torch.bfloat16, device=gu.device)
+    _check(lib().tkv_swiglu(rows, two // 2, gu.data_ptr(), out.data_ptr(), _stream(stream)))
+    return out
 
 
 def tkv_cd_sample(logits: torch.Tensor, temperature: float, draw_off: torch.Tensor, uniform: torch.Tensor,

@@ -5,17 +5,19 @@ Every candidate row (one per distinct candidate, computation deduplication Sec. 
 last token through L layers of pre-norm attention and a SwiGLU MLP -- the layer layout of the
 paper's Qwen2.5 and Llama-3 generators (Sec. 5.1) -- and ends in next-token logits.  Per layer:
 
-    h = RMSNorm(x);  q, k, v = h Wqkv;  q, k = RoPE(q, k, position)
-    tkv_kv_append: the new token's k, v go to its pool slot          (library kernel)
-    o = tree attention over the row's block table (tkv_decode)        (library kernel)
-    x += o Wo;  h = RMSNorm(x);  x += (SiLU(h Wg) * (h Wu)) Wd
+    h = RMSNorm(x)                                                   (tkv_add_rmsnorm)
+    q, k, v = h Wqkv;  q, k = RoPE(q, k, position), and the new
+    token's k, v go to its pool slot                                 (tkv_rope_append)
+    o = tree attention over the row's block table                    (tkv_decode)
+    x += o Wo;  h = RMSNorm(x)                                       (tkv_add_rmsnorm)
+    x += (SiLU(h Wg) * (h Wu)) Wd                                    (tkv_swiglu; the add with the next norm)
 
 then logits = RMSNorm(x) W_lm, and the CD branching sampler draws each row's potential-many tokens
 (tkv_cd_sample, library kernel).  One plan serves every layer: the block tables are the same in all
 of them, only the pools differ.
 
-The dense products are plain GEMMs and run in the platform BLAS (hipBLASLt through torch.mm); the
-norms, RoPE and SiLU are elementwise torch ops.  Precision: the residual stream and every
+The dense products are plain GEMMs and run in the platform BLAS (hipBLASLt through torch.mm); what lies
+between them are library kernels of one pass over memory each.  Precision: the residual stream and every
 elementwise step are fp32; every GEMM takes bf16 operands, accumulates in fp32 and rounds its
 output to bf16 (as the attention kernel rounds o).  No biases; weights are N(0, 1/fan_in).
 """
@@ -25,7 +27,7 @@ from typing import List, NamedTuple
 
 import torch
 
-from . import Plan, tkv_cd_sample, tkv_kv_append
+from . import Plan, tkv_add_rmsnorm, tkv_cd_sample, tkv_rope_append, tkv_swiglu
 
 
 class DecoderShape(NamedTuple):
@@ -72,17 +74,6 @@ class SyntheticDecoder:
         half = s.d // 2
         self.inv_freq = s.rope_theta ** (-torch.arange(half, dtype=torch.float32, device=device) * 2.0 / s.d)
 
-    # ------------------------------------------------------------------ pieces
-    def _rms(self, x, w):
-        return (x * torch.rsqrt((x * x).mean(-1, keepdim=True) + self.shape.eps) * w).to(torch.bfloat16)
-
-    def _rope(self, t, cos, sin):
-        """Rotate-half RoPE of [rows, heads, d] bf16 at fp32, rounded back to bf16."""
-        half = t.shape[-1] // 2
-        x = t.float()
-        x1, x2 = x[..., :half], x[..., half:]
-        return torch.cat((x1 * cos - x2 * sin, x2 * cos + x1 * sin), dim=-1).to(torch.bfloat16).contiguous()
-
     # ------------------------------------------------------------------ one step
     def step(self, tokens: torch.Tensor, positions: torch.Tensor, dst: torch.Tensor, plan: Plan,
              k_pools: List[torch.Tensor], v_pools: List[torch.Tensor], stream=None, on_layer=None) -> torch.Tensor:
@@ -95,24 +86,19 @@ class SyntheticDecoder:
         s = self.shape
         rows = int(tokens.numel())
         ang = positions.float()[:, None] * self.inv_freq[None, :]
-        cos, sin = torch.cos(ang)[:, None, :], torch.sin(ang)[:, None, :]
-        x = self.embed[tokens]
-        nq, nk = s.hq * s.d, s.hkv * s.d
+        cos, sin = torch.cos(ang), torch.sin(ang)
+        x, delta = self.embed[tokens], None  # the residual stream, and what is still to be added to it
         for li, w in enumerate(self.layers):
-            qkv = torch.mm(self._rms(x, w["ln1"]), w["wqkv"])
-            q = self._rope(qkv[:, :nq].reshape(rows, s.hq, s.d), cos, sin)
-            k = self._rope(qkv[:, nq:nq + nk].reshape(rows, s.hkv, s.d), cos, sin)
-            v = qkv[:, nq + nk:].reshape(rows, s.hkv, s.d).contiguous()
-            tkv_kv_append(dst, k, v, k_pools[li], v_pools[li], stream)
+            qkv = torch.mm(tkv_add_rmsnorm(x, delta, w["ln1"], s.eps), w["wqkv"])
+            q = tkv_rope_append(qkv, cos, sin, dst, s.hq, k_pools[li], v_pools[li], stream)
             o = torch.empty((rows, s.hq, s.d), dtype=torch.bfloat16, device=x.device)
             plan.decode(q, k_pools[li], v_pools[li], o, None, stream)
-            x = x + torch.mm(o.view(rows, nq), w["wo"]).float()
-            gu = torch.mm(self._rms(x, w["ln2"]), w["wgu"]).float()
-            a = (torch.nn.functional.silu(gu[:, :s.inter]) * gu[:, s.inter:]).to(torch.bfloat16)
-            x = x + torch.mm(a, w["wd"]).float()
+            delta = torch.mm(o.view(rows, s.hq * s.d), w["wo"])
+            gu = torch.mm(tkv_add_rmsnorm(x, delta, w["ln2"], s.eps), w["wgu"])
+            delta = torch.mm(tkv_swiglu(gu), w["wd"])
             if on_layer:
                 on_layer(li)
-        return torch.mm(self._rms(x, self.lnf), self.lm).float()
+        return torch.mm(tkv_add_rmsnorm(x, delta, self.lnf, s.eps), self.lm).float()
 
     def sample(self, logits, temperature, draw_off, uniform, max_potential, stream=None):
         """The CD branching step on the logits: (tokens, counts, groups per row)."""
