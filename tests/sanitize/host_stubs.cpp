@@ -30,6 +30,19 @@ TKV_EXPORT int tkv_kv_append(const tkv_shape*, const int32_t*, int32_t, const vo
     tkv::clear_error();
     return tkv::set_error(TKV_EHIP, "tkv_kv_append: host-only build, no device");
 }
+TKV_EXPORT int tkv_add_rmsnorm(int32_t, int32_t, float, float*, const void*, const float*, void*, void*) {
+    tkv::clear_error();
+    return tkv::set_error(TKV_EHIP, "tkv_add_rmsnorm: host-only build, no device");
+}
+TKV_EXPORT int tkv_rope_append(const tkv_shape*, int32_t, const void*, const float*, const float*, const int32_t*, void*,
+                               void*, void*, void*) {
+    tkv::clear_error();
+    return tkv::set_error(TKV_EHIP, "tkv_rope_append: host-only build, no device");
+}
+TKV_EXPORT int tkv_swiglu(int32_t, int32_t, const void*, void*, void*) {
+    tkv::clear_error();
+    return tkv::set_error(TKV_EHIP, "tkv_swiglu: host-only build, no device");
+}
 TKV_EXPORT int tkv_cd_sample(int32_t, int32_t, float, int32_t, const float*, const float*, const int32_t*, int32_t, int32_t*,
                              int32_t*, int32_t*, void*) {
     tkv::clear_error();
