@@ -195,3 +195,25 @@ def test_decode_loop_end_to_end(seed, hq, hkv, d):
     print(f"    decode loop: {n} rows, {skipped} skipped writes; max {err.max():.2e} mean {err.mean():.2e} "
           f"lse {lerr.max():.2e}", flush=True)
     assert np.isfinite(err).all() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS and lerr.max() <= LSE_ABS
+
+
+@pytest.mark.parametrize("hkv,d", [(8, 128), (16, 64)])
+@pytest.mark.parametrize("over", [-1, 0, 5])
+def test_append_on_both_sides_of_the_streaming_size(hkv, d, over):
+    # calls of 256 MiB (read and written) and more go past the caches: one token less, exactly that, more
+    import paper_2609_39334_amd as tkv
+    n = (256 << 20) // (hkv * d * 8) + over
+    g = torch.Generator(device="cuda").manual_seed(7)
+    nb = -(-n // 16) + 3
+    dst = torch.randperm(nb * 16, generator=g, device="cuda")[:n].int()
+    dst[::5] = -1
+    new = torch.randn((2, n, hkv, d), generator=g, device="cuda").bfloat16()
+    pools = torch.full((2, nb, hkv, 16, d), -3.0, dtype=torch.bfloat16, device="cuda")
+    want = pools.clone()
+    keep = dst >= 0
+    at = dst[keep].long()
+    for i in range(2):
+        want[i][at // 16, :, at % 16] = new[i][keep]
+    tkv.tkv_kv_append(dst, new[0], new[1], pools[0], pools[1])
+    torch.cuda.synchronize()
+    assert torch.equal(pools, want)
