@@ -20,6 +20,8 @@
 // tile items: wide tiles (multi-token verify rows, wide shared chunks, G > 16): one workgroup of
 //             four waves per item, 128 rows (32 per wave) against 64-key stages of K/V
 //             double-buffered through LDS.
+// attn_tile8 runs the tile items of small verification batches, eight waves each, sharing the rows and
+// the keys of a tile.
 // merge_partials: log-sum-exp merge of the partial results of a query token's chunks:
 //             lse = log sum_j exp(lse_j),  o = sum_j exp(lse_j - lse) o_j.
 
@@ -35,12 +37,17 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8_t, u); }
 
 __device__ __forceinline__ f32x4_t mfma_16x16x32(bf16x8_t a, bf16x8_t b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x16_t mfma_32x32x16(bf16x8_t a, bf16x8_t b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -569,6 +576,17 @@ constexpr int tile_buf_bytes() {
     return 64 * D * 2;
 }
 
+// The same for the 32-row waves of tile_item32, whose operand reads differ: K, 32 rows of one chunk; V
+// transposed, 4 rows of 64 contiguous bytes per 32 lanes.  Zero bank-conflict cycles measured.
+template <int D>
+__device__ __forceinline__ int tile_swz_k32(int r) {
+    return D == 128 ? r & 15 : (r >> 1) & 7;
+}
+template <int D>
+__device__ __forceinline__ int tile_swz_v32(int r) {
+    return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1);
+}
+
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
 // Fetch one block of a stage straight from global memory into LDS (buffer_load_dwordx4 ... lds:
@@ -579,7 +597,7 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 // which forces every later LDS read to wait for all earlier ones.)  Rows past the block's length
 // read its last row (masked later); a block past the item's end has len 0 and reads row 0 of a
 // valid block.  kdst / vdst: the block's rows in the stage buffers (uniform).
-template <int D>
+template <int D, bool W32>
 __device__ __forceinline__ void stage_fetch(const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool,
                                             size_t boff, int len, int lane, uint8_t* kdst, uint8_t* vdst) {
     constexpr int CPR = D / 8;     // 16-byte chunks per row
@@ -592,8 +610,8 @@ __device__ __forceinline__ void stage_fetch(const uint16_t* __restrict__ kpool, 
     for (int i = 0; i < 16 / RPI; ++i) {
         const int r = i * RPI + lane / CPR;
         const int row_off = min(r, last) * D * 2;
-        const int koff = row_off + (((lane % CPR) ^ tile_swz_k<D>(r)) * 16);
-        const int voff = row_off + (((lane % CPR) ^ tile_swz_v<D>(r)) * 16);
+        const int koff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_k32<D>(r) : tile_swz_k<D>(r))) * 16);
+        const int voff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_v32<D>(r) : tile_swz_v<D>(r))) * 16);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void_ptr)(kdst + i * 1024), 16, koff, 0, 0, 0);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void_ptr)(vdst + i * 1024), 16, voff, 0, 0, 0);
     }
@@ -608,19 +626,20 @@ __device__ __forceinline__ void stage_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// One workgroup per tile item: a tile of up to 64T query rows (wave w owns rows 16Tw .. 16Tw+16T-1
-// as T column tiles) against the item's key blocks, four blocks per stage.  Stage s+1 is fetched into
+// One workgroup of four waves per tile item: a tile of up to 128 query rows (wave w owns rows
+// 32w .. 32w+31 as two column tiles of 16) against the item's key blocks, four blocks per stage.  Stage s+1 is fetched into
 // the other pair of LDS buffers while stage s is contracted; one barrier per stage (a buffer is
 // rewritten only after every wave has passed the barrier that follows its last use).  The stage
 // loop is unrolled by two so that each stage names its buffers statically: the compiler then knows
 // that the reads of one buffer do not depend on the fetch into the other.
-template <int D, int T>
+template <int D>
 __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::TokDesc* __restrict__ toks,
                                           const tkv::BlkDesc* __restrict__ blks, const uint16_t* __restrict__ q,
                                           const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool,
                                           uint16_t* __restrict__ o, float* __restrict__ lse, uint16_t* __restrict__ po,
                                           float* __restrict__ plse, int hq, int hkv, int G, float sl2, uint8_t* k0,
                                           uint8_t* v0, uint8_t* k1, uint8_t* v1) {
+    constexpr int T = 2;
     constexpr int RB = 2 * D;  // bytes per K/V row in the stage buffers
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -661,10 +680,10 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
     // block descriptors of a stage: lane l holds block 4s + (l & 3) (the item's last block past its end)
     auto stage_desc = [&](int st) { return bd[min(4 * st + (lane & 3), nb - 1)]; };
     int2 dcur = stage_desc(0), dnxt = stage_desc(1);
-    const int wblk = wave * 16 * RB;  // this wave's block within a stage buffer (waves 0-3 fetch)
-    if (wave < 4) {
+    const int wblk = wave * 16 * RB;  // this wave's block within a stage buffer
+    {
         const int len = wave < nb ? __builtin_amdgcn_readlane(dcur.y, wave) : 0;
-        stage_fetch<D>(kpool, vpool, static_cast<size_t>(__builtin_amdgcn_readlane(dcur.x, wave)) * blk_stride + kvh_off,
+        stage_fetch<D, false>(kpool, vpool, static_cast<size_t>(__builtin_amdgcn_readlane(dcur.x, wave)) * blk_stride + kvh_off,
                        len, lane, k0 + wblk, v0 + wblk);
     }
     WaveAcc<D, T> A;
@@ -673,10 +692,10 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
     auto stage = [&](int st, const uint8_t* ks, const uint8_t* vs, uint8_t* kn, uint8_t* vn) {
         stage_barrier();
         // fetch the next stage while this one is contracted
-        if (st + 1 < n_stages && wave < 4) {
+        if (st + 1 < n_stages) {
             const int bn = 4 * (st + 1) + wave;
             const int len = bn < nb ? __builtin_amdgcn_readlane(dnxt.y, wave) : 0;
-            stage_fetch<D>(kpool, vpool,
+            stage_fetch<D, false>(kpool, vpool,
                            static_cast<size_t>(__builtin_amdgcn_readlane(dnxt.x, wave)) * blk_stride + kvh_off, len,
                            lane, kn + wblk, vn + wblk);
         }
@@ -790,6 +809,280 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
     }
 }
 
+// Normalise a wave's 32 query rows and write them, as write_rows does: lane (col, hi) holds columns
+// 32dt + 8q + 4hi + 0..3 of row col in acc[dt][4q ..], and one exchange with lane col + 32 gives each
+// lane eight contiguous columns, one 16-byte store.
+template <int D>
+__device__ __forceinline__ void write_rows32(const f32x16_t (&acc)[D / 32], float m, float l, bool ok, int qtok, int h,
+                                             int slot, int hi, uint16_t* __restrict__ o, float* __restrict__ lse,
+                                             uint16_t* __restrict__ po, float* __restrict__ plse, int hq, float sl2) {
+    const float l_tot = l + __shfl_xor(l, 32);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const float lse_v = l_tot > 0.f ? (m * sl2 + log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
+    const bool fin = slot < 0;
+    uint16_t* row = (fin ? o + (static_cast<size_t>(qtok) * hq + h) * D : po + (static_cast<size_t>(slot) * hq + h) * D) + 8 * hi;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int qp = 0; qp < 2; ++qp) {
+            uint32_t w[2][2];  // [quad of the pair][columns 0-1, 2-3]
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    const float a = acc[dt][8 * qp + 4 * x + 2 * y] * inv, b = acc[dt][8 * qp + 4 * x + 2 * y + 1] * inv;
+                    w[x][y] = fin ? pack_bf16x2(a, b) : pack_f16x2(a, b);
+                }
+            const auto e0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+            const auto e1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+            if (ok) *reinterpret_cast<u32x4_t*>(row + 32 * dt + 16 * qp) = u32x4_t{e0[0], e1[0], e0[1], e1[1]};
+        }
+    if (ok && hi == 0) {
+        if (!fin)
+            plse[static_cast<size_t>(slot) * hq + h] = lse_v;
+        else if (lse)
+            lse[static_cast<size_t>(qtok) * hq + h] = lse_v;
+    }
+}
+
+// One workgroup of NG x R waves per tile item: a tile of up to 32R query rows (wave w of each group owns
+// rows 32w .. 32w+31, lane (col, hi) row 32w + col) against the item's key blocks, NG x R blocks per stage
+// (one fetched by each wave), R of them contracted by each of the NG groups.
+// Stage s+1 is fetched into the other pair of LDS buffers while stage s is contracted; one barrier
+// per stage (a buffer is rewritten only after every wave has passed the barrier that follows its last
+// use).  The stage loop is unrolled by two so that each stage names its buffers statically: the
+// compiler then knows that the reads of one buffer do not depend on the fetch into the other.
+template <int D, int NG, int R>
+__device__ __forceinline__ void tile_item32(const tkv::ItemDesc& it, const tkv::TokDesc* __restrict__ toks,
+                                            const tkv::BlkDesc* __restrict__ blks, const uint16_t* __restrict__ q,
+                                            const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool,
+                                            uint16_t* __restrict__ o, float* __restrict__ lse, uint16_t* __restrict__ po,
+                                            float* __restrict__ plse, int hq, int hkv, int G, float sl2, uint8_t* k0,
+                                            uint8_t* v0, uint8_t* k1, uint8_t* v1, float* xml) {
+    constexpr int RB = 2 * D;  // bytes per K/V row in the stage buffers
+    const int lane = threadIdx.x & 63;
+    constexpr int NB = NG * R;  // blocks per stage
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = wid % R, grp = wid / R;
+    const int col = lane & 31, hi = lane >> 5;
+    const size_t blk_stride = static_cast<size_t>(hkv) * (16 * D);
+    const size_t kvh_off = static_cast<size_t>(it.kvh) * (16 * D);
+    const int2* bd = reinterpret_cast<const int2*>(blks + it.blk_off);
+    const int nb = it.n_blk;
+    const int n_stages = (nb + NB - 1) / NB;
+
+    // this lane's query row (only Q and the causal limit stay live across the stages; the output
+    // fields are read again from the token descriptor at the end)
+    bf16x8_t qf[D / 16];
+    int limit;
+    {
+        const int row = 32 * wave + col;
+        const int t = row / G;
+        const tkv::TokDesc td = toks[it.tok_off + min(t, it.n_tok - 1)];
+        limit = t < it.n_tok ? td.limit : -1;
+        const uint16_t* qrow = q + (static_cast<size_t>(td.qtok) * hq + it.kvh * G + (row - t * G)) * D + hi * 8;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qrow + ks * 16));
+    }
+    const bool wave_active = __builtin_amdgcn_ballot_w64(limit >= 0) != 0;
+
+    // Swizzled read offsets (bytes).  K, S^T A operand: lane (col, hi) reads row col of a block pair,
+    // chunk 2ks + hi, i.e. koff ^ 32ks.  V, transposed reads: lane (16 lanes j of dims half ds, hi)
+    // reads row 4hi + j/4 of a block (and row 8 + 4hi + j/4), 8 bytes of dims 32dt + 16ds + 4(j & 3),
+    // i.e. voff ^ 64dt (and 8 rows further).  (The XORs touch only the chunk-index bits.)
+    const int koff = col * RB + 16 * (hi ^ tile_swz_k32<D>(col));
+    const int vj = lane & 15, vrow = 4 * hi + (vj >> 2);
+    const int voff = vrow * RB + 16 * ((2 * ((lane >> 4) & 1) + ((vj & 3) >> 1)) ^ tile_swz_v32<D>(vrow)) + 8 * (vj & 1);
+
+    // block descriptors of a stage: lane l holds block NB s + l % NB (the item's last block past its end)
+    auto stage_desc = [&](int st) { return bd[min(NB * st + lane % NB, nb - 1)]; };
+    int2 dcur = stage_desc(0), dnxt = stage_desc(1);
+    const int wblk = wid * 16 * RB;      // the block this wave fetches, within a stage buffer
+    const int gblk = grp * R * 16 * RB;  // and its group's first
+    {
+        const int len = wid < nb ? __builtin_amdgcn_readlane(dcur.y, wid) : 0;
+        stage_fetch<D, true>(kpool, vpool,
+                             static_cast<size_t>(__builtin_amdgcn_readlane(dcur.x, wid)) * blk_stride + kvh_off, len,
+                             lane, k0 + wblk, v0 + wblk);
+    }
+    f32x16_t acc[D / 32];
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) acc[dt] = f32x16_t{};
+    float m = -INFINITY, l = 0.f;
+    int pos = it.pos0;
+    auto stage = [&](int st, const uint8_t* ks, const uint8_t* vs, uint8_t* kn, uint8_t* vn) {
+        stage_barrier();
+        // fetch the next stage while this one is contracted
+        if (st + 1 < n_stages) {
+            const int len = NB * (st + 1) + wid < nb ? __builtin_amdgcn_readlane(dnxt.y, wid) : 0;
+            stage_fetch<D, true>(kpool, vpool,
+                                 static_cast<size_t>(__builtin_amdgcn_readlane(dnxt.x, wid)) * blk_stride + kvh_off, len,
+                                 lane, kn + wblk, vn + wblk);
+        }
+        const int2 dthis = dcur;
+        dcur = dnxt;
+        dnxt = stage_desc(st + 2);
+        const int first = NB * st + R * grp;  // the group's first block of the stage
+        if (!wave_active || first >= nb) return;
+        // the lengths of the group's blocks, and the key positions where they start: the other groups'
+        // blocks lie before and after (a block past the item's end counts to no position that is used)
+        int len[R], bpos[R], stage_end = pos;
+        bool full = true;
+        if constexpr (NG > 1) {
+#pragma unroll
+            for (int b = 0; b < NB - R; ++b) stage_end += b < R * grp ? __builtin_amdgcn_readlane(dthis.y, b) : 0;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) pos += __builtin_amdgcn_readlane(dthis.y, b);
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int lj = __builtin_amdgcn_readlane(dthis.y, R * grp + j);
+            len[j] = first + j < nb ? lj : 0;
+            full = full && len[j] == 16;
+            bpos[j] = stage_end;
+            stage_end += len[j];
+        }
+        if constexpr (NG == 1) pos = stage_end;
+        // S^T of the block pairs first, so that the softmax below overlaps MFMAs still in flight:
+        // sc[g][8b + 4u + x] is key 8u + 4hi + x of block 2g + b
+        constexpr int P = R / 2;
+        f32x16_t sc[P];
+#pragma unroll
+        for (int g = 0; g < P; ++g) sc[g] = f32x16_t{};
+        bf16x8_t kf[D / 16][P];
+#pragma unroll
+        for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+            for (int g = 0; g < P; ++g)
+                kf[kk][g] = *reinterpret_cast<const bf16x8_t*>(ks + gblk + 32 * g * RB + (koff ^ (32 * kk)));
+#pragma unroll
+        for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+            for (int g = 0; g < P; ++g) sc[g] = mfma_32x32x16(kf[kk][g], qf[kk], sc[g]);
+        // K reads eight operands ahead of the MFMAs that use them
+        constexpr int kReads = D / 16 * P, kAhead = kReads < 8 ? kReads : 8;
+        __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+        for (int kk = 0; kk < (kReads - kAhead) / 4; ++kk) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
+        // one uniform decision per stage: mask only if a block is partial or absent, or some row's
+        // causal limit falls inside the stage
+        const bool cut = limit >= 0 && limit < stage_end - 1;
+        if (!full || __builtin_amdgcn_ballot_w64(cut) != 0) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int vlen = min(len[j], limit - bpos[j] + 1) - 4 * hi;
+#pragma unroll
+                for (int x = 0; x < 8; ++x)
+                    if (8 * (x >> 2) + (x & 3) >= vlen) sc[j >> 1][8 * (j & 1) + x] = -INFINITY;
+            }
+        }
+        // the exponent base moves only when the stage's maximum exceeds it by more than 2^8 in
+        // probability scale (then O and l are rescaled): each lane tests its own scores, and the row
+        // maximum over the two lanes of a row is taken only when some lane needs the base moved
+        {
+            constexpr float kSlack = 8.f;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int g = 0; g < P; ++g)
+#pragma unroll
+                for (int x = 0; x < 16; x += 2) mx = fmaxf(mx, fmaxf(sc[g][x], sc[g][x + 1]));
+            if (__builtin_amdgcn_ballot_w64(mx > m + kSlack / sl2) != 0) {  // false for mx = -inf; true for m = -inf < mx
+                const auto e = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+                const float m_new = fmaxf(m, fmaxf(__uint_as_float(e[0]), __uint_as_float(e[1])));
+                const float alpha = m == m_new ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * sl2);
+                l *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < D / 32; ++dt) acc[dt] *= alpha;
+                m = m_new;
+            }
+        }
+        const float msc = m == -INFINITY ? 0.f : m * sl2;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            float pr[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) pr[x] = __builtin_amdgcn_exp2f(fmaf(sc[j >> 1][8 * (j & 1) + x], sl2, -msc));
+            const uint4 pk{pack_bf16x2(pr[0], pr[1]), pack_bf16x2(pr[2], pr[3]), pack_bf16x2(pr[4], pr[5]),
+                           pack_bf16x2(pr[6], pr[7])};
+            // the row sum over the bf16-rounded P that the PV product uses, two keys per v_dot2
+            l = sum_bf16x2(pk.x, sum_bf16x2(pk.y, sum_bf16x2(pk.z, sum_bf16x2(pk.w, l))));
+            const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, pk);
+            const uint8_t* vr = vs + gblk + 16 * j * RB;
+#pragma unroll
+            for (int dt = 0; dt < D / 32; ++dt) {
+                const int off = voff ^ (64 * dt);
+                const s16x4_t va = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4_t*)(const_cast<uint8_t*>(vr + off)));
+                const s16x4_t vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4_t*)(const_cast<uint8_t*>(vr + 8 * RB + off)));
+                const bf16x8_t vab = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7));
+                acc[dt] = mfma_32x32x16(vab, pb, acc[dt]);
+            }
+        }
+    };
+    for (int st = 0; st < n_stages; st += 2) {
+        stage(st, k0, v0, k1, v1);
+        if (st + 1 < n_stages) stage(st + 1, k1, v1, k0, v0);
+    }
+    if constexpr (NG > 1) {
+        // The other groups' results over their keys join the first's, relative to the largest base.  They
+        // pass through the stage buffers, 32 x D fp32 a wave: two waves' to an array.
+        __syncthreads();  // every wave is done with the stage buffers
+        static_assert((NG - 1) * R <= 8 && 32 * D * 4 <= NB * 16 * RB / 2, "the results fit the four arrays");
+        auto slot = [&](int x) {
+            uint8_t* a = x < 2 ? k0 : x < 4 ? v0 : x < 6 ? k1 : v1;
+            return reinterpret_cast<float*>(a + (x & 1) * (32 * D * 4)) + lane * 4;
+        };
+        if (grp > 0) {
+            const int x = (grp - 1) * R + wave;
+            float* xa = slot(x);
+#pragma unroll
+            for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    *reinterpret_cast<f32x4_t*>(xa + (4 * dt + u) * 256) =
+                        f32x4_t{acc[dt][4 * u], acc[dt][4 * u + 1], acc[dt][4 * u + 2], acc[dt][4 * u + 3]};
+            xml[x * 128 + lane] = m;
+            xml[x * 128 + 64 + lane] = l;
+        }
+        __syncthreads();
+        if (grp > 0) return;
+        float mt = m;
+#pragma unroll
+        for (int g = 0; g < NG - 1; ++g) mt = fmaxf(mt, xml[(g * R + wave) * 128 + lane]);
+        const float a0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - mt) * sl2);
+        l *= a0;
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt) acc[dt] *= a0;
+#pragma unroll 1  // one group's result in registers at a time
+        for (int g = 0; g < NG - 1; ++g) {
+            const int x = g * R + wave;
+            const float mg = xml[x * 128 + lane];
+            const float ag = mg == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mg - mt) * sl2);
+            l = fmaf(xml[x * 128 + 64 + lane], ag, l);
+            const float* xa = slot(x);
+#pragma unroll
+            for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const f32x4_t b = *reinterpret_cast<const f32x4_t*>(xa + (4 * dt + u) * 256);
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) acc[dt][4 * u + y] = fmaf(b[y], ag, acc[dt][4 * u + y]);
+                }
+        }
+        m = mt;
+    }
+    if (!wave_active) return;
+    const int row = 32 * wave + col;
+    const int t = row / G;
+    const tkv::TokDesc td = toks[it.tok_off + min(t, it.n_tok - 1)];
+    write_rows32<D>(acc, m, l, t < it.n_tok, td.qtok, it.kvh * G + (row - t * G), td.slot, hi, o, lse, po, plse, hq, sl2);
+}
+
 
 // The attention kernel runs tile items (one workgroup each, longest first, in the planner's XCD
 // order) and the wave grid (kWaveWG waves per workgroup) in one launch, so neither waits for the
@@ -802,7 +1095,15 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
 // the kinds with period 2 per XCD, which locks each kind onto two of the four engines.)  Then come
 // the remaining tile items, then the remaining wave-grid workgroups.  Either way tile item i and
 // wave workgroup j run on XCDs i % 8 and j % 8, as the planner assumed.
-template <int D>
+// W32: the tile items run on v_mfma_f32_32x32x16_bf16 (tile_item32) or 16x16x32 (tile_item).  The larger
+// instruction takes half the issue slots: 5% fewer cycles on every plan measured.  But it reads and writes
+// the accumulators twice as often per flop, and where tiles keep the whole chip busy for long the power
+// limit sets the time: eight queries' step verification (4,000 tile items) ran 1.72 M cycles at 1.97 GHz
+// with 16x16x32, 1.64 M at 1.82 GHz with 32x32x16.  So plans of up to kTile32MaxItems tile items (two
+// rounds of the chip's workgroup slots, the second mostly a tail) take 32x32x16: 1,632 candidates under
+// eight prompts (720 items) 65.0 -> 62.0 us, the speculative tree 102.7 -> 101.1 us; larger ones keep
+// 16x16x32 (step verification 780 against 816 us, the serving batch 4.31 against 4.43 ms).
+template <int D, bool W32>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd(
     const tkv::ItemDesc* __restrict__ items, int n_tile, int n_wave_wg, int runs, const tkv::TokDesc* __restrict__ toks,
     const tkv::BlkDesc* __restrict__ blks, const int4* __restrict__ wdesc, const int32_t* __restrict__ woff,
@@ -832,8 +1133,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (tile >= 0) {
         if (tile >= n_tile) return;
         const tkv::ItemDesc it = items[tile];
-        tile_item<D, 2>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1,
-                        lds_v1);
+        if constexpr (W32)
+            tile_item32<D, 1, 4>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0,
+                                 lds_k1, lds_v1, nullptr);
+        else
+            tile_item<D>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1,
+                         lds_v1);
         return;
     }
     if (wg >= n_wave_wg) return;
@@ -845,23 +1150,32 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 }
 
 // Few tile items and no wave-grid work (a small verification batch): the chip has a CU for every
-// tile, and a tile's walk over its keys sets the call's time.  Eight waves of one 16-row column tile
-// each share a 128-row tile (instead of four waves of two), so each wave does half the MFMA and
-// softmax work per stage and the walk is shorter.  Waves 0-3 fetch the stages.
-template <int D>
+// tile, and a tile's walk over its keys sets the call's time.  Eight waves share a tile: R waves of 32
+// rows, times 8 / R groups of waves that each take a part of every stage's keys with a softmax of their
+// own and join at the end, so the walk is half as many stages as four waves make of it.  R = 4 (128 rows,
+// two groups of 64 keys a stage): every stage buffer is read by four waves of 32 rows, where eight waves
+// of 16 rows read each of them eight times.  R = 2 (64 rows, four groups of 32 keys a stage): half the
+// work for a CU, where the chip has CUs for twice the tiles.  Bound by a stage's chain (LDS reads ->
+// scores -> maxima -> exponentials -> PV) with two waves per SIMD.  512 tokens of 28/4/128 heads under
+// 1,024 keys and more: 29.6 us as eight waves of 16 rows, 28.6 us with R = 4 (116 tiles), 23.8 us with
+// R = 2 (228 tiles).
+template <int D, int R>
 __global__ __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_tile8(
     const tkv::ItemDesc* __restrict__ items, int n_tile, const tkv::TokDesc* __restrict__ toks,
     const tkv::BlkDesc* __restrict__ blks, const uint16_t* __restrict__ q, const uint16_t* __restrict__ kpool,
     const uint16_t* __restrict__ vpool, uint16_t* __restrict__ o, float* __restrict__ lse, uint16_t* __restrict__ po,
     float* __restrict__ plse, int hq, int hkv, int G, float sl2) {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_k0[tile_buf_bytes<D>()];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_v0[tile_buf_bytes<D>()];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_k1[tile_buf_bytes<D>()];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_v1[tile_buf_bytes<D>()];
+    // two stage buffers of K and V (eight blocks each), which take the groups' results at the end
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_k0[2 * tile_buf_bytes<D>()];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_v0[2 * tile_buf_bytes<D>()];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_k1[2 * tile_buf_bytes<D>()];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_v1[2 * tile_buf_bytes<D>()];
+    __shared__ float lds_ml[8 * 128];
     const int b = blockIdx.x;
     if (b >= n_tile) return;
     const tkv::ItemDesc it = items[b];
-    tile_item<D, 1>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1, lds_v1);
+    tile_item32<D, 8 / R, R>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1,
+                             lds_v1, lds_ml);
 }
 
 // Log-sum-exp merge of one query token's partials (one workgroup per token, whose partial slots
@@ -1033,13 +1347,13 @@ static int launch_d(const tkv_plan* p, uint8_t* ws, const void* q, const void* k
                                     std::max(0, (n_wave_wg + 7) / 8 * 8 - R * runs)
                               : (n_tile + 7) / 8 * 8 + (n_wave_wg + 7) / 8 * 8;
     if (p->tile8 && n_wave_wg == 0 && n_tile > 0)
-        hipExtLaunchKernelGGL(attn_tile8<D>, dim3(static_cast<unsigned>(n_tile)), dim3(2 * kThreads), 0, st,
+        hipExtLaunchKernelGGL((p->tile_rows == kTileRowsSmall ? attn_tile8<D, 2> : attn_tile8<D, 4>), dim3(static_cast<unsigned>(n_tile)), dim3(2 * kThreads), 0, st,
                               ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, 0, items, n_tile, toks, blks,
                               static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                               static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,
                               p->group, sl2);
     else if (grid > 0)
-        hipExtLaunchKernelGGL(attn_fwd<D>, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, st,
+        hipExtLaunchKernelGGL((n_tile <= kTile32MaxItems ? attn_fwd<D, true> : attn_fwd<D, false>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, st,
                               ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, 0, items, n_tile, n_wave_wg, runs, toks, blks,
                               wdesc, woff, wtiles, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                               static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,

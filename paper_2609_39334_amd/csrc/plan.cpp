@@ -251,6 +251,7 @@ void clear_plan(tkv_plan* p) {
     p->wave_off.clear();
     p->wave_tiles.clear();
     p->n_slots = 0;
+    p->tile_rows = 0;
     p->tile8 = false;
     p->off_items = p->off_toks = p->off_blks = p->off_merges = p->off_mslots = p->off_wdesc = p->off_woff = p->off_wtiles = 0;
     p->off_po = p->off_plse = p->desc_bytes = p->total_bytes = 0;
@@ -403,7 +404,20 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         tkv_plan_stats& st = p->stats;
         st.n_rows = n_rows;
         st.n_qtok = n_rows ? q_indptr[n_rows] : 0;
-        const int32_t tpt = tkv::kTileRowsWG / G;  // query tokens per workgroup-kernel tile
+        // A batch of verify rows only, so small that the chip has a CU for every tile of kTileRowsSmall
+        // rows, takes tiles of that size; every other plan's tiles have kTileRowsWG rows.  (512 tokens of
+        // 28/4 heads, 228 tiles of 64 rows or 116 of 128: 23.8 against 28.6 us.  Past one tile per CU the
+        // smaller tiles would only read the keys twice as often.)
+        const int64_t tile8_max = opt(&tkv_plan_options::tile8_max_items, tkv::kTile8MaxItems);
+        p->tile_rows = tkv::kTileRowsSmall;
+        {
+            const int64_t limit = std::min<int64_t>(tile8_max, tkv::kTile8MaxItems), per = tkv::kTileRowsSmall / G;
+            int64_t n = 0;
+            for (int32_t r = 0; r < n_rows && n <= limit; ++r)
+                n = static_cast<int64_t>(L[r]) * G < tkv::kTileRows ? limit + 1 : n + (L[r] + per - 1) / per * s.hkv;
+            if (n > limit) p->tile_rows = tkv::kTileRowsWG;
+        }
+        const int32_t tpt = p->tile_rows / G;  // query tokens per workgroup-kernel tile
 
         // ------------------------------------------------------------ accounting
         {
@@ -924,9 +938,8 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         st.n_items_wave = static_cast<int32_t>(p->wave_items.size());
         st.n_waves = static_cast<int32_t>(p->wave_tiles.size());
         st.n_idle_waves = static_cast<int32_t>(std::count(p->wave_tiles.begin(), p->wave_tiles.end(), 0));
-        // a plan of a few tile items and nothing else gives each tile a CU to itself: its 128 rows then
-        // run as eight 16-row waves, which shortens the tile's walk
-        const int64_t tile8_max = opt(&tkv_plan_options::tile8_max_items, tkv::kTile8MaxItems);
+        // a plan of a few tile items and nothing else gives each tile a CU to itself: eight waves then
+        // share the tile's rows and keys, which shortens its walk
         p->tile8 = p->wave_items.empty() && !p->items.empty() && static_cast<int64_t>(p->items.size()) <= tile8_max;
         st.n_slots = p->n_slots;
         st.n_merge = static_cast<int32_t>(p->merges.size());
@@ -1183,6 +1196,7 @@ void swap_contents(tkv_plan* a, tkv_plan* b) {
     swap(a->wave_off, b->wave_off);
     swap(a->wave_tiles, b->wave_tiles);
     swap(a->n_slots, b->n_slots);
+    swap(a->tile_rows, b->tile_rows);
     swap(a->tile8, b->tile8);
     swap(a->off_items, b->off_items);
     swap(a->off_toks, b->off_toks);

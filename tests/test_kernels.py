@@ -304,9 +304,44 @@ def _small_verify(seed, shape, n_ctx=2, n_cands=5):
                                            (44, 64, 1, 128), (45, 6, 2, 64)])
 @pytest.mark.parametrize("tile8_max", [0, 100000])
 def test_small_verify_batches_on_both_tile_kernels(seed, hq, hkv, d, tile8_max):
-    # a verify-only batch makes tile items alone; a few of them run as 8-wave workgroups (one 16-row
-    # column tile per wave), more of them on the 4-wave kernel -- the option forces either
+    # a verify-only batch makes tile items alone; a few of them run as 8-wave workgroups (rows and keys
+    # split over the waves), more of them on the 4-wave kernel -- the option forces either
     wl = _small_verify(seed, W.Shape(hq, hkv, d))
     b, st = compare(wl, 0, options={"tile8_max_items": tile8_max})
     assert st["n_items_wave"] == 0 and st["n_items_row"] > 0 and st["n_items"] == st["n_items_row"]
 
+
+@pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 4, 64)])
+@pytest.mark.parametrize("tokens", [300, 750, 2000, 5200])
+def test_verify_tile_variants_at_their_edges(hq, hkv, d, tokens):
+    # rows of 1 to 20 blocks (key groups without a key, partial stages and blocks), whole and partial
+    # tiles, in batches of each tile variant: 64-row tiles with four key groups, 128-row tiles with two,
+    # and the 4-wave kernel on either matrix instruction (up to and past 1,024 tile items)
+    g = hq // hkv
+    wl = W.Workload(f"tile_edges_{tokens}", W.Shape(hq, hkv, d), 50, note="verify-only batch")
+    rt = np.random.default_rng([50, tokens])
+    lengths = [n for n in (10, 16, 17, 31, 32, 33, 48, 64, 65, 100, 128, 130, 145, 257, 272) if n * g >= 64]
+    ctx = [-1] + [wl.extend(-1, rt.integers(0, 32000, n), True) for n in (5, 16, 47, 100)]
+    cands, total = [], 0
+    while total < tokens:
+        n = min(lengths[len(cands) % len(lengths)], tokens)
+        cands.append((wl.extend(ctx[len(cands) % len(ctx)], rt.integers(0, 32000, n), True), n))
+        total += n
+    for c in ctx[1:]:
+        wl.prune(c)
+    wl.launch("verify", cands)
+    wl.finalize()
+    b, o, lse, k, v, q, st, same = run_gpu(wl, 0, repeat=2)
+    v32 = W.bf16_bits_to_f32(v)
+    r = oracle_check(q, W.bf16_bits_to_f32(k), v32, b.tables, b.block_len, b.q_lens, o, lse)
+    # the first tokens of a row see a few keys, and nothing averages the roundings out: o is a mean of values
+    # of up to vmax, rounded to bf16 (2^-8), with weights rounded to bf16 (2^-8 of each, against their own
+    # sum: 2^-8 x 2 vmax); lse sums the rounded weights (2^-8)
+    vmax = np.nanmax(np.abs(v32))
+    assert same and r["finite"] and r["max"] <= 3 * 2.0 ** -8 * vmax and r["mean"] <= MEAN_ABS
+    assert r["lse_max"] <= 2.0 ** -8
+    small, full = (sum(-(-n // (rows // g)) for n in b.q_lens) * hkv for rows in (64, 128))
+    assert st["n_items_wave"] == 0 and st["n_items"] == (small if small <= 256 else full)
+    variant = 0 if small <= 256 else 1 if full <= 256 else 2 if full <= 1024 else 3
+    assert variant == {(300, 7): 0, (750, 7): 1, (2000, 7): 2, (5200, 7): 3,
+                       (300, 4): 0, (750, 4): 0, (2000, 4): 2, (5200, 4): 2}[(tokens, g)]
