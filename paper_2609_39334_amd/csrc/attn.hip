@@ -1095,7 +1095,15 @@ __device__ __forceinline__ void tile_item32(const tkv::ItemDesc& it, const tkv::
 // the kinds with period 2 per XCD, which locks each kind onto two of the four engines.)  Then come
 // the remaining tile items, then the remaining wave-grid workgroups.  Either way tile item i and
 // wave workgroup j run on XCDs i % 8 and j % 8, as the planner assumed.
-template <int D>
+// W32: the tile items run on v_mfma_f32_32x32x16_bf16 (tile_item32) or 16x16x32 (tile_item).  The larger
+// instruction takes half the issue slots: 5% fewer cycles on every plan measured.  But it reads and writes
+// the accumulators twice as often per flop, and where tiles keep the whole chip busy for long the power
+// limit sets the time: eight queries' step verification (4,000 tile items) ran 1.72 M cycles at 1.97 GHz
+// with 16x16x32, 1.64 M at 1.82 GHz with 32x32x16.  So plans of up to kTile32MaxItems tile items (two
+// rounds of the chip's workgroup slots, the second mostly a tail) take 32x32x16: 1,632 candidates under
+// eight prompts (720 items) 65.0 -> 62.0 us, the speculative tree 102.7 -> 101.1 us; larger ones keep
+// 16x16x32 (step verification 780 against 816 us, the serving batch 4.31 against 4.43 ms).
+template <int D, bool W32>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd(
     const tkv::ItemDesc* __restrict__ items, int n_tile, int n_wave_wg, int runs, const tkv::TokDesc* __restrict__ toks,
     const tkv::BlkDesc* __restrict__ blks, const int4* __restrict__ wdesc, const int32_t* __restrict__ woff,
@@ -1125,7 +1133,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (tile >= 0) {
         if (tile >= n_tile) return;
         const tkv::ItemDesc it = items[tile];
-        tile_item<D>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1, lds_v1);
+        if constexpr (W32)
+            tile_item32<D, 1, 4>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0,
+                                 lds_k1, lds_v1, nullptr);
+        else
+            tile_item<D>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1,
+                         lds_v1);
         return;
     }
     if (wg >= n_wave_wg) return;
@@ -1340,7 +1353,7 @@ static int launch_d(const tkv_plan* p, uint8_t* ws, const void* q, const void* k
                               static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,
                               p->group, sl2);
     else if (grid > 0)
-        hipExtLaunchKernelGGL(attn_fwd<D>, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, st,
+        hipExtLaunchKernelGGL((n_tile <= kTile32MaxItems ? attn_fwd<D, true> : attn_fwd<D, false>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, st,
                               ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, 0, items, n_tile, n_wave_wg, runs, toks, blks,
                               wdesc, woff, wtiles, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                               static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,

@@ -36,6 +36,7 @@ constexpr int kWaveWorkers = 2048;  // waves of the wave kernel: 2 workgroups of
 constexpr int kWaveWG = 4;      // waves per workgroup of the wave kernel (independent; no barriers)
 constexpr int kTile8MaxItems = 256;  // tile items (and no wave grid) up to which 8-wave workgroups run them: one per CU
 constexpr int kTileRowsSmall = 64;   // rows of a tile of a batch so small that the chip has a CU for every such tile
+constexpr int kTile32MaxItems = 1024;  // tile items up to which attn_fwd contracts them with 32x32x16 MFMAs (two rounds of the slots)
 constexpr int kInterleaveRun = 32;   // workgroups per run when tile items and wave-grid workgroups alternate:
                                      // 8 XCDs x 4 shader engines, one workgroup of a kind per engine
 constexpr int32_t kNoLimit = 1 << 30;  // causal limit of a q_len-1 token: it sees its whole path (kv_len <= 2^30)
