@@ -232,8 +232,10 @@ size_t tkv_plan_workspace_bytes(const tkv_plan* plan);
  * the descriptor region between uploads.  The library records an event after the copy and waits
  * for it before the plan's host memory changes or is recycled (tkv_plan_update, the next upload,
  * tkv_plan_destroy), so a plan may be updated or destroyed right after an upload; those calls may
- * then wait for the work enqueued on hip_stream before the copy.  EINVAL (size, alignment, NULL),
- * EHIP. */
+ * then wait for the work enqueued on hip_stream before the copy.  Descriptors of up to 256 KiB
+ * usually pass through one of four pinned slots per GPU (1 MiB, held until the process ends) and
+ * need no such wait; under stream capture, or with every slot in flight, they are copied from the
+ * plan as larger ones are.  EINVAL (size, alignment, NULL), EHIP. */
 int tkv_plan_upload(tkv_plan* plan, void* d_workspace, size_t bytes, void* hip_stream);
 
 void tkv_plan_destroy(tkv_plan* plan);

@@ -30,6 +30,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <mutex>
 #include "internal.h"
 
@@ -1247,6 +1248,72 @@ __global__ __launch_bounds__(256) void patch_apply(const int2* __restrict__ pair
     }
 }
 
+// Copies a plan's image from host memory that the device can read (n 16-byte words).
+__global__ __launch_bounds__(256) void image_copy(const u32x4_t* __restrict__ src, u32x4_t* __restrict__ dst, int n) {
+    const int i = static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x);
+    if (i < n) dst[i] = src[i];
+}
+
+constexpr int kMaxDevices = 64;
+
+// Pinned slots that small images pass through on their way to the device, per device: at most
+// kStageSlots of kStageBytes, made on the first upload and kept for the life of the process.  A slot is
+// taken again once the kernel that read it has ended; while all are taken, uploads copy from the image.
+constexpr int kStageSlots = 4;
+constexpr size_t kStageBytes = size_t{256} << 10;
+struct StageSlot {
+    void* host = nullptr;
+    hipEvent_t done = nullptr;
+    bool used = false;  // `done` was recorded
+    bool held = false;  // between take and give
+};
+struct StagePool {
+    std::mutex m;
+    bool tried[kMaxDevices] = {};
+    StageSlot slots[kMaxDevices][kStageSlots];
+};
+StagePool& stage_pool() {
+    static StagePool* pool = new StagePool();  // never destroyed: no HIP call after the runtime's own end
+    return *pool;
+}
+
+StageSlot* take_stage() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+    StagePool& pool = stage_pool();
+    std::lock_guard<std::mutex> lock(pool.m);
+    StageSlot* slots = pool.slots[dev];
+    if (!pool.tried[dev]) {
+        pool.tried[dev] = true;
+        for (int i = 0; i < kStageSlots; ++i) {
+            if (hipHostMalloc(&slots[i].host, kStageBytes, hipHostMallocDefault) != hipSuccess ||
+                hipEventCreateWithFlags(&slots[i].done, hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();  // not an error of the upload: it copies from the image
+                if (slots[i].host) (void)hipHostFree(slots[i].host);
+                slots[i].host = nullptr;
+                break;
+            }
+        }
+    }
+    for (int i = 0; i < kStageSlots; ++i) {
+        StageSlot& s = slots[i];
+        if (!s.host || s.held) continue;
+        if (s.used && hipEventQuery(s.done) != hipSuccess) {
+            (void)hipGetLastError();  // hipErrorNotReady
+            continue;
+        }
+        s.held = true;
+        return &s;
+    }
+    return nullptr;
+}
+
+void give_stage(StageSlot* s, bool recorded) {
+    std::lock_guard<std::mutex> lock(stage_pool().m);
+    s->used = s->used || recorded;
+    s->held = false;
+}
+
 }  // namespace
 
 namespace tkv {
@@ -1258,14 +1325,21 @@ void wait_copies(const tkv_plan* p) {
     }
 }
 
-// Records the completion of the copies just enqueued from the plan's host memory.
-static int record_copy(const tkv_plan* p, hipStream_t st, const char* fn) {
+// The plan's event, made on its first upload (the no-allocation call records with it, and makes none).
+static int make_copy_event(const tkv_plan* p, const char* fn) {
     if (!p->copy_event) {
         hipEvent_t e;
         const hipError_t rc = hipEventCreateWithFlags(&e, hipEventDisableTiming);
         if (rc != hipSuccess) return set_error(TKV_EHIP, "%s: hipEventCreateWithFlags: %s", fn, hipGetErrorString(rc));
         p->copy_event = e;
     }
+    return TKV_OK;
+}
+
+// Records the completion of the copies just enqueued from the plan's host memory.
+static int record_copy(const tkv_plan* p, hipStream_t st, const char* fn) {
+    const int made = make_copy_event(p, fn);
+    if (made != TKV_OK) return made;
     const hipError_t rc = hipEventRecord(static_cast<hipEvent_t>(p->copy_event), st);
     if (rc != hipSuccess) return set_error(TKV_EHIP, "%s: hipEventRecord: %s", fn, hipGetErrorString(rc));
     p->copy_pending = true;
@@ -1303,6 +1377,41 @@ int upload(tkv_plan* p, void* d_ws, size_t bytes, void* stream) {
                                reinterpret_cast<const int2*>(ws + p->off_patch), n, reinterpret_cast<int32_t*>(ws));
             e = hipGetLastError();
             if (e != hipSuccess) return set_error(TKV_EHIP, "tkv_plan_upload: patch_apply launch: %s", hipGetErrorString(e));
+        }
+    }
+    // A small image goes through a pinned slot and a copy kernel: the stream then runs kernel after kernel,
+    // where a copy from pageable memory is staged by the runtime and handed to a copy engine, with a wait
+    // on either side; and the plan's own memory is free at once, so that destroying the plan does not wait
+    // for the stream.  A flush of 2,048 tokens (a 57-KB image; its attention kernel takes 56 us), planned
+    // and run anew each time: 75.5 us a flush by the runtime's copy, 60.8 us this way.  Larger images
+    // keep the copy engine, which moves them without holding compute units.  (A stream being captured takes the plain copy: a slot is not
+    // the graph's to keep.)
+    if (!patch && p->desc_bytes && p->desc_bytes <= kStageBytes) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        const bool known = hipStreamIsCapturing(st, &cap) == hipSuccess;
+        if (!known) (void)hipGetLastError();  // not an error of the upload
+        StageSlot* slot = known && cap == hipStreamCaptureStatusNone ? take_stage() : nullptr;
+        if (slot) {
+            const int made = make_copy_event(p, "tkv_plan_upload");
+            if (made != TKV_OK) {
+                give_stage(slot, false);
+                return made;
+            }
+            std::memcpy(slot->host, p->image.get(), p->desc_bytes);
+            const int n = static_cast<int>(p->desc_bytes / 16);  // sections are 256-byte aligned
+            hipLaunchKernelGGL(image_copy, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st,
+                               static_cast<const u32x4_t*>(slot->host), static_cast<u32x4_t*>(d_ws), n);
+            hipError_t e = hipGetLastError();
+            const bool launched = e == hipSuccess;
+            if (launched) e = hipEventRecord(slot->done, st);
+            if (launched && e != hipSuccess) (void)hipStreamSynchronize(st);  // the slot is free again either way
+            give_stage(slot, launched && e == hipSuccess);
+            if (e != hipSuccess) return set_error(TKV_EHIP, "tkv_plan_upload: image_copy: %s", hipGetErrorString(e));
+            p->d_ws = d_ws;
+            p->ws_image = d_ws;
+            p->dirty.clear();
+            p->dirty_over = false;
+            return TKV_OK;
         }
     }
     if (!patch && p->desc_bytes) {
@@ -1399,7 +1508,6 @@ static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 static_assert(TKV_NOALLOC_MAX_BYTES == kScratchBytes, "header limit and device array agree");
 
 namespace {
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 

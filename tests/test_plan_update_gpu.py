@@ -108,3 +108,41 @@ def test_plan_destroyed_right_after_upload():
     assert img2 != img
     assert ws[:len(img)].cpu().numpy().tobytes() == img
     tkv.tkv_plan_destroy(h2)
+
+
+@pytest.mark.parametrize("rows", [5, 500])
+def test_many_uploads_in_flight(rows):
+    # images of either side of the staging slots' 256 KiB, more of them in flight than there are slots, from
+    # two threads on streams of their own: every workspace holds its own plan's descriptors
+    import threading
+    import paper_2609_39334_amd as tkv
+    tree = DecodeTree(24, W.Shape(12, 2, 128), [3 + 7 * i % 300 for i in range(rows)], num_blocks=65536)
+    qi, made = tree.q_indptr(), [[], []]
+    tables = []
+    for _ in range(10):
+        tree.step()
+        tables.append(tree.tables()[1:])
+
+    def work(out):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            busy = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
+            for ki, kb, bl in tables:
+                for _ in range(4):
+                    busy.add_(1)
+                h = tkv.tkv_plan_create(tree.dims(), qi, ki, kb, bl)
+                ws = torch.empty(tkv.tkv_plan_workspace_bytes(h), dtype=torch.uint8, device="cuda")
+                tkv.tkv_plan_upload(h, ws, stream.cuda_stream)
+                out.append((tkv.tkv_plan_image(h)[0], ws))
+                tkv.tkv_plan_destroy(h)
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(out,)) for out in made]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(len(out) == len(tables) for out in made)
+    for img, ws in made[0] + made[1]:
+        assert (len(img) <= 256 << 10) == (rows == 5)
+        assert ws[:len(img)].cpu().numpy().tobytes() == img
