@@ -44,6 +44,12 @@ namespace {
 
 constexpr int kChunkBlocks = 16;      // longest key run of a narrow shared item (256 tokens)
 constexpr int kChunkBlocksWide = 64;  // longest key run of a wide (128-row tile) shared item
+// In a plan of fewer than kShortItems tile items, half the CUs: as short as it takes to make that many, down
+// to kShortBlocks (four stages: an item's start and its partials take as long as three).  108 rows of 12/2
+// heads under four prompts of 1,237 (56 tile items, 104 in short chunks): 20.5 -> 17.6 us.  Batches past it lose: 16 queries of 32 rows
+// under 512-token prompts (192 tile items) take 31.7 us, 35.0 us in chunks of 16 blocks.
+constexpr int kShortItems = 128;
+constexpr int kShortBlocks = 16;
 constexpr int kFoldBlocks = 16;       // longest shared segment folded into its children's key runs
 static_assert(kChunkBlocks <= tkv::kWaveBlocks, "a wave item holds its key blocks in one record");
 
@@ -576,6 +582,28 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
                 folded[p] = 1;
             }
         }
+        // Shared segments on the tiles of a batch that makes few tile items are cut shorter, into about
+        // kShortItems items in all: each takes a CU, and walks its keys in a shorter time.
+        int32_t wide_blocks = chunk_wide;
+        if (!opts || opts->wide_chunk_blocks < 0) {
+            int64_t items = 0, work = 0;  // work: key blocks x tiles x KV heads
+            for (int32_t r = 0; r < n_rows; ++r)
+                if (static_cast<int64_t>(L[r]) * G >= tkv::kTileRows) items += static_cast<int64_t>((L[r] + tpt - 1) / tpt) * s.hkv;
+            const int64_t row_items = items;
+            for (size_t si = 0; si < segs.size(); ++si) {
+                const Segment& sg = segs[si];
+                int64_t tok = 0;
+                for (int32_t r : sg.rows) tok += L[r];
+                if (folded[si] || sg.rows.size() < 2 || (G <= tkv::kWaveRows && tok * G <= wave_max_rows)) continue;
+                const int64_t tiles = (tok + tpt - 1) / tpt * s.hkv, nb = static_cast<int64_t>(sg.nodes.size());
+                items += (nb + chunk_wide - 1) / chunk_wide * tiles;
+                work += nb * tiles;
+            }
+            if (work > 0 && items < kShortItems) {
+                const int64_t n = (work / (kShortItems - row_items) + 3) / 4 * 4;  // whole 64-key stages
+                wide_blocks = static_cast<int32_t>(std::min<int64_t>(chunk_wide, std::max<int64_t>(kShortBlocks, n)));
+            }
+        }
         std::vector<Chunk> chunks;
         std::vector<BlkDesc>& seg_blks = sc.seg_blks;  // each segment's key blocks, in path order
         seg_blks.clear();
@@ -625,7 +653,7 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
             if (sg.rows.size() == 1)
                 tile_full(nb, wide ? chunk_wide : kChunkBlocks, cut);
             else
-                tile_evenly(nb, wide ? chunk_wide : kChunkBlocks, cut);
+                tile_evenly(nb, wide ? wide_blocks : kChunkBlocks, cut);
         }
         // partial slots for tokens covered by more than one chunk: each token's slots are
         // contiguous (in chunk order), so the merge reads a token's partials as one range.  A

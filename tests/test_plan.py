@@ -256,3 +256,22 @@ def test_plans_do_not_depend_on_earlier_plans():
             got = (plan.image(), plan.stats)
             assert seen.setdefault(name, got) == got, name
             del plan
+
+
+@pytest.mark.parametrize("blocks,rows,n_items", [
+    (15, 20, 2), (16, 20, 2), (17, 20, 4), (64, 20, 8), (65, 20, 10),  # fewer than 128 items: chunks of 16
+    (1000, 24, 64 * 2), (1023, 24, 64 * 2),    # and of ceil(work / 128 items), in whole 64-key stages
+    (4160, 20, 65 * 2),                        # 128 items and more at 64 blocks: as long as ever
+])
+def test_wide_chunks_of_small_plans(blocks, rows, n_items):
+    # rows of one token and a block of their own under one shared prompt of `blocks`
+    import paper_2609_39334_amd as tkv
+    nb = blocks + rows
+    kb = np.concatenate([np.concatenate([np.arange(blocks), [blocks + r]]) for r in range(rows)]).astype(np.int32)
+    qi = np.arange(rows + 1, dtype=np.int32)
+    plan = tkv.Plan((12, 2, 128, 16, nb), qi, qi * (blocks + 1), kb, np.full(nb, 16, np.int32), upload=False)
+    wide = [it for it in plan.view()["items"] if it[6] == 0]   # tile items over shared chunks
+    assert len(wide) == n_items
+    # every chunk's keys are contracted once per KV head, each tile's rows within 128
+    assert sum(it[4] for it in wide) == 2 * blocks * -(-rows // 21)
+    assert all(it[2] * 6 <= 128 for it in wide)
