@@ -50,6 +50,8 @@ constexpr int kChunkBlocksWide = 64;  // longest key run of a wide (128-row tile
 // under 512-token prompts (192 tile items) take 31.7 us, 35.0 us in chunks of 16 blocks.
 constexpr int kShortItems = 128;
 constexpr int kShortBlocks = 16;
+constexpr int64_t kShortPartialBytes = int64_t{8} << 20;  // and only while the partials are few: no plan outgrows
+                                                          // the no-allocation call's workspace by being cut shorter
 constexpr int kFoldBlocks = 16;       // longest shared segment folded into its children's key runs
 static_assert(kChunkBlocks <= tkv::kWaveBlocks, "a wave item holds its key blocks in one record");
 
@@ -601,7 +603,17 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
             }
             if (work > 0 && items < kShortItems) {
                 const int64_t n = (work / (kShortItems - row_items) + 3) / 4 * 4;  // whole 64-key stages
-                wide_blocks = static_cast<int32_t>(std::min<int64_t>(chunk_wide, std::max<int64_t>(kShortBlocks, n)));
+                const int64_t len = std::min<int64_t>(chunk_wide, std::max<int64_t>(kShortBlocks, n));
+                int64_t slots = n_rows;  // at most as many partials, with the rows' spare ones
+                for (size_t si = 0; si < segs.size(); ++si) {
+                    const Segment& sg = segs[si];
+                    int64_t tok = 0;
+                    for (int32_t r : sg.rows) tok += L[r];
+                    const bool wide = G > tkv::kWaveRows || tok * G > wave_max_rows;
+                    const int64_t most = !wide ? kChunkBlocks : sg.rows.size() < 2 ? chunk_wide : len;
+                    if (!folded[si]) slots += (static_cast<int64_t>(sg.nodes.size()) + most - 1) / most * tok;
+                }
+                if (slots * s.hq * (2 * s.d + 4) <= kShortPartialBytes) wide_blocks = static_cast<int32_t>(len);
             }
         }
         std::vector<Chunk> chunks;
