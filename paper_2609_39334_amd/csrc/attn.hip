@@ -416,7 +416,7 @@ struct WaveList {
 // flight while the current pair is contracted; the pair goes through one 32-key online-softmax
 // step with a lazily moved base and through PV on v_mfma_f32_16x16x32_bf16.
 template <int D, int T>
-__device__ __forceinline__ void wave_run_pair(const int4* __restrict__ wdesc, const WaveList& L,
+__device__ __forceinline__ void wave_run_pair(int4 dc, const int4* __restrict__ wdesc, const WaveList& L,
                                               const uint16_t* __restrict__ q, const uint16_t* __restrict__ kpool,
                                               const uint16_t* __restrict__ vpool, uint16_t* __restrict__ o,
                                               float* __restrict__ lse, uint16_t* __restrict__ po,
@@ -428,7 +428,6 @@ __device__ __forceinline__ void wave_run_pair(const int4* __restrict__ wdesc, co
     const uint8_t* vra = vs + (4 * kg + (col >> 2)) * VROW + (4 * (col & 3)) * 2;
     const uint8_t* vrb = vra + 16 * VROW;
 
-    int4 dc = wdesc[static_cast<size_t>(L.at(0)) * kRecWords + (lane & (kRecWords - 1))];
     int4 dn = wdesc[static_cast<size_t>(L.at(1)) * kRecWords + (lane & (kRecWords - 1))];
     bf16x8_t qf[T][D / 32];
     int kvh_c, nb_c, limit[T];
@@ -545,13 +544,16 @@ __device__ __forceinline__ void wave_worker(int w, int lane, const int4* __restr
                                             const uint16_t* __restrict__ vpool, uint16_t* __restrict__ o,
                                             float* __restrict__ lse, uint16_t* __restrict__ po, float* __restrict__ plse,
                                             int hq, int hkv, int G, float sl2, uint8_t* vs) {
+    // its first record (record w, whatever the wave is to do) is on its way while its width and list are read:
+    // one round of memory latency less at every wave's start (16 queries of 32 candidates: 40.95 -> 40.44 us)
+    const int4 dc = wdesc[static_cast<size_t>(w) * kRecWords + (lane & (kRecWords - 1))];
     const int T = wtiles[w];
     if (T == 0) return;
     const WaveList L{w, woff[w], woff[w + 1] - woff[w] + 1};
     if (T == 1)
-        wave_run_pair<D, 1>(wdesc, L, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, vs, lane);
+        wave_run_pair<D, 1>(dc, wdesc, L, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, vs, lane);
     else
-        wave_run_pair<D, 2>(wdesc, L, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, vs, lane);
+        wave_run_pair<D, 2>(dc, wdesc, L, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, vs, lane);
 }
 
 // ============================================================================ tile kernel
