@@ -7,6 +7,7 @@
 //   O^T += V^T P^T  v_mfma_f32_16x16x32_bf16 over two blocks at a time (A = V^T of both blocks read
 //                   transposed from LDS with ds_read_b64_tr_b16, B = P^T exactly as the two S^T
 //                   results sit in the lanes),
+// (tile items of small batches on v_mfma_f32_32x32x16_bf16, one block at a time: tile_item32)
 // with an online softmax in between (exp2 with the scale folded into one FMA; the exponent base of
 // a row moves only when its maximum grows by more than 2^8, so O is rarely rescaled).  Keys past a
 // block's length are never loaded (row reads are clamped to the block's last token and masked) and

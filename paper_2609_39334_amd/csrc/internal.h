@@ -21,7 +21,7 @@ void clear_error();
 // ------------------------------------------------------------------ device descriptors
 constexpr int kBlock = 16;     // tokens per KV block
 constexpr int kTileRows = 64;     // rows (q_len x G) from which a row is verified whole, not through segments
-constexpr int kTileRowsWG = 128;  // query rows of a workgroup-kernel tile (4 waves x 2 column tiles x 16)
+constexpr int kTileRowsWG = 128;  // query rows of a workgroup-kernel tile (4 waves of 32)
 constexpr int kItemShared = 0;  // tile of several rows' tokens over one segment chunk (workgroup kernel)
 constexpr int kItemRow = 1;     // tile of one row's tokens over its whole path (workgroup kernel)
 constexpr int kItemWave = 2;    // tile of <= 16 T rows over one segment chunk (wave kernel)
