@@ -585,37 +585,34 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
             }
         }
         // Shared segments on the tiles of a batch that makes few tile items are cut shorter, into about
-        // kShortItems items in all: each takes a CU, and walks its keys in a shorter time.  Every tile item
-        // counts, those of segments that only one row reads too (they are not cut shorter).
+        // kShortItems items in all: each takes a CU, and walks its keys in a shorter time.
         int32_t wide_blocks = chunk_wide;
         if (!opts || opts->wide_chunk_blocks < 0) {
-            int64_t fixed = 0, items = 0, work = 0;  // work: the shared segments' key blocks x tiles x KV heads
-            int64_t slots = n_rows;  // at most as many partials besides the shared tile segments', with the rows' spare ones
+            int64_t items = 0, work = 0;  // work: key blocks x tiles x KV heads
             for (int32_t r = 0; r < n_rows; ++r)
-                if (static_cast<int64_t>(L[r]) * G >= tkv::kTileRows) fixed += static_cast<int64_t>((L[r] + tpt - 1) / tpt) * s.hkv;
-            std::vector<std::pair<int64_t, int64_t>> shared;  // (key blocks, tokens) of each shared segment on the tiles
+                if (static_cast<int64_t>(L[r]) * G >= tkv::kTileRows) items += static_cast<int64_t>((L[r] + tpt - 1) / tpt) * s.hkv;
+            const int64_t row_items = items;
             for (size_t si = 0; si < segs.size(); ++si) {
-                if (folded[si]) continue;
                 const Segment& sg = segs[si];
                 int64_t tok = 0;
                 for (int32_t r : sg.rows) tok += L[r];
-                const bool wide = G > tkv::kWaveRows || tok * G > wave_max_rows;
-                const int64_t nb = static_cast<int64_t>(sg.nodes.size()), most = wide ? chunk_wide : kChunkBlocks;
-                const int64_t n = (nb + most - 1) / most, tiles = (tok + tpt - 1) / tpt * s.hkv;
-                if (!wide || sg.rows.size() < 2) {
-                    slots += n * tok;
-                    if (wide) fixed += n * tiles;
-                    continue;
-                }
-                shared.emplace_back(nb, tok);
-                items += n * tiles;
+                if (folded[si] || sg.rows.size() < 2 || (G <= tkv::kWaveRows && tok * G <= wave_max_rows)) continue;
+                const int64_t tiles = (tok + tpt - 1) / tpt * s.hkv, nb = static_cast<int64_t>(sg.nodes.size());
+                items += (nb + chunk_wide - 1) / chunk_wide * tiles;
                 work += nb * tiles;
             }
-            if (work > 0 && fixed + items < kShortItems) {
-                // a cap of whole 64-key stages (an even cut below it takes as many stages as its longest chunk)
-                const int64_t n = (work / (kShortItems - fixed) + 3) / 4 * 4;
+            if (work > 0 && items < kShortItems) {
+                const int64_t n = (work / (kShortItems - row_items) + 3) / 4 * 4;  // whole 64-key stages
                 const int64_t len = std::min<int64_t>(chunk_wide, std::max<int64_t>(kShortBlocks, n));
-                for (const auto& sh : shared) slots += (sh.first + len - 1) / len * sh.second;
+                int64_t slots = n_rows;  // at most as many partials, with the rows' spare ones
+                for (size_t si = 0; si < segs.size(); ++si) {
+                    const Segment& sg = segs[si];
+                    int64_t tok = 0;
+                    for (int32_t r : sg.rows) tok += L[r];
+                    const bool wide = G > tkv::kWaveRows || tok * G > wave_max_rows;
+                    const int64_t most = !wide ? kChunkBlocks : sg.rows.size() < 2 ? chunk_wide : len;
+                    if (!folded[si]) slots += (static_cast<int64_t>(sg.nodes.size()) + most - 1) / most * tok;
+                }
                 if (slots * s.hq * (2 * s.d + 4) <= kShortPartialBytes) wide_blocks = static_cast<int32_t>(len);
             }
         }

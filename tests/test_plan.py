@@ -275,52 +275,3 @@ def test_wide_chunks_of_small_plans(blocks, rows, n_items):
     # every chunk's keys are contracted once per KV head, each tile's rows within 128
     assert sum(it[4] for it in wide) == 2 * blocks * -(-rows // 21)
     assert all(it[2] * 6 <= 128 for it in wide)
-
-
-def _candidates(hq, hkv, prompts, rows, q_len, prompt_blocks, tail_blocks, **kw):
-    """`rows` rows of q_len tokens under each of `prompts` prompts, each row with blocks of its own."""
-    import paper_2609_39334_amd as tkv
-    tables, nb = [], 0
-    for _ in range(prompts):
-        prompt = list(range(nb, nb + prompt_blocks))
-        nb += prompt_blocks
-        for _ in range(rows):
-            tables.append(prompt + list(range(nb, nb + tail_blocks)))
-            nb += tail_blocks
-    ki = np.cumsum([0] + [len(t) for t in tables]).astype(np.int32)
-    qi = np.arange(len(tables) + 1, dtype=np.int32) * q_len
-    return tkv.Plan((hq, hkv, 128, 16, nb), qi, ki, np.concatenate(tables).astype(np.int32), np.full(nb, 16, np.int32),
-                    upload=False, **kw)
-
-
-@pytest.mark.parametrize("batch,n_items,n_slots", [
-    # short verify rows of 56 and 48 query rows: their own blocks are tile items too
-    ((28, 4, 2, 15, 8, 64, 4), 176, 480), ((32, 8, 2, 8, 12, 64, 4), 176, 384),
-    ((32, 1, 2, 64, 1, 128, 4), 192, 384),     # groups of 32 heads: every chunk is tile items
-])
-def test_single_row_segments_count_among_a_plans_tile_items(batch, n_items, n_slots):
-    # 128 tile items and more in all: no segment is cut into short chunks
-    plan, asked = _candidates(*batch), _candidates(*batch, options={"wide_chunk_blocks": 64})
-    assert (plan.stats["n_items"], plan.stats["n_slots"]) == (n_items, n_slots)
-    assert plan.image() == asked.image()
-
-
-@pytest.mark.parametrize("batch,chunks", [
-    ((28, 4, 1, 5, 8, 64, 4), {16}),           # 20 row-tail items and few shared ones: short chunks
-    ((32, 1, 1, 8, 1, 65, 4), {13}),           # five even chunks (four stages of 64 keys each)
-    ((12, 2, 1, 24, 1, 77, 1), {13, 16}),      # four of 16 and the rest
-])
-def test_short_chunks_are_cut_evenly(batch, chunks):
-    plan = _candidates(*batch)
-    assert plan.stats["n_items"] < 256
-    n = {it[4] for it in plan.view()["items"] if it[6] == 0 and it[4] > batch[6]}
-    assert n == chunks
-
-
-def test_short_chunks_only_while_the_partials_are_few():
-    # 50 prompts of 64 blocks, one tile item each: 128 such items would be cut shorter, but for the row's
-    # partials (rows x heads x (d fp16 + an fp32 lse)), which stay within 8 MiB
-    few, many = (_candidates(16, 1, 50, 8, 1, 64, tail) for tail in (1, 4 * 16 * 12))
-    shared = [{it[4] for it in p.view()["items"] if it[6] == 0 and it[2] == 8} for p in (few, many)]
-    assert many.stats["n_slots"] * 16 * 260 > 8 << 20
-    assert max(shared[0]) < 64 and max(shared[1]) == 64
