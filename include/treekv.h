@@ -209,7 +209,8 @@ int tkv_plan_create(const tkv_shape* shape, int32_t n_rows, const int32_t* q_ind
  *                    8-wave workgroups (default 256); a plan of verify rows alone that makes at
  *                    most as many items (and at most 256) of 64-row tiles takes 64-row tiles
  *   wide_chunk_blocks  longest key run, in blocks, of a shared chunk on the 128-row tiles
- *                    (default 64, and down to 16 in plans of fewer than 128 tile items)
+ *                    (default 64, and down to 16 in plans whose shared chunks and whole
+ *                    rows make fewer than 128 tile items)
  *   fold_blocks      a shared segment on the 128-row tiles of at most this many blocks, whose child
  *                    segments all go to the 128-row tiles and hold all of its rows, is read as the
  *                    head of each child's key run instead of on its own (default 16; 0: never) */

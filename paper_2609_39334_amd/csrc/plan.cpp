@@ -44,10 +44,15 @@ namespace {
 
 constexpr int kChunkBlocks = 16;      // longest key run of a narrow shared item (256 tokens)
 constexpr int kChunkBlocksWide = 64;  // longest key run of a wide (128-row tile) shared item
-// In a plan of fewer than kShortItems tile items, half the CUs: as short as it takes to make that many, down
-// to kShortBlocks (four stages: an item's start and its partials take as long as three).  108 rows of 12/2
-// heads under four prompts of 1,237 (56 tile items, 104 in short chunks): 20.5 -> 17.6 us.  Batches past it lose: 16 queries of 32 rows
-// under 512-token prompts (192 tile items) take 31.7 us, 35.0 us in chunks of 16 blocks.
+// In a plan where shared segments and whole rows make fewer than kShortItems tile items, half the CUs: as
+// short as it takes to make that many, down to kShortBlocks (four stages: an item's start and its partials take
+// as long as three).  108 rows of 12/2 heads under four prompts of 1,237 (56 tile items, 104 in short chunks):
+// 20.5 -> 17.6 us.  Batches past it lose: 16 queries of 32 rows under 512-token prompts (192 tile items) take
+// 31.7 us, 35.0 us in chunks of 16 blocks.  Segments of one row (tile items for groups of more than 16 heads
+// and in short verify rows) do not count, being short mostly: 30 rows of 8 tokens of 28/4 heads under two
+// prompts of 64 blocks, with four blocks of their own, take 25.5 us as 176 items, 19.5 us as 288.  What they
+// walk does: with 64 blocks of their own, 60 rows of 9 tokens of 12/2 heads take 27 us as 172 items (64-block
+// prompt), 38 us as 276, which are also too many for attn_tile8; with 32 blocks both take about the same.
 constexpr int kShortItems = 128;
 constexpr int kShortBlocks = 16;
 constexpr int64_t kShortPartialBytes = int64_t{8} << 20;  // and only while the partials are few: no plan outgrows
@@ -584,36 +589,58 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
                 folded[p] = 1;
             }
         }
-        // Shared segments on the tiles of a batch that makes few tile items are cut shorter, into about
-        // kShortItems items in all: each takes a CU, and walks its keys in a shorter time.
+        // Shared segments on the tiles of a batch where they and the whole rows make few tile items are cut
+        // shorter, into about kShortItems such items: each takes a CU, and walks its keys in a shorter time.
+        // Where every tile item has a CU of its own, the longest walk that stays as it is (a whole row's, a
+        // one-row segment's) sets the call's time: no chunk is cut shorter than that, and a cut that gives
+        // the plan more items than CUs has to be worth half a long chunk's walk.
         int32_t wide_blocks = chunk_wide;
         if (!opts || opts->wide_chunk_blocks < 0) {
-            int64_t items = 0, work = 0;  // work: key blocks x tiles x KV heads
+            int64_t row_items = 0, one_row_items = 0, items = 0, work = 0;  // work: the shared ones' key blocks x tiles x KV heads
+            int64_t longest = kShortBlocks;
+            int64_t slots = n_rows;  // at most as many partials besides the shared tile segments', with the rows' spare ones
             for (int32_t r = 0; r < n_rows; ++r)
-                if (static_cast<int64_t>(L[r]) * G >= tkv::kTileRows) items += static_cast<int64_t>((L[r] + tpt - 1) / tpt) * s.hkv;
-            const int64_t row_items = items;
+                if (static_cast<int64_t>(L[r]) * G >= tkv::kTileRows) {
+                    row_items += static_cast<int64_t>((L[r] + tpt - 1) / tpt) * s.hkv;
+                    longest = std::max<int64_t>(longest, in.row_len[r]);
+                }
+            struct Shared {
+                int64_t nb, tok, tiles;
+            };
+            std::vector<Shared> shared;
             for (size_t si = 0; si < segs.size(); ++si) {
+                if (folded[si]) continue;
                 const Segment& sg = segs[si];
                 int64_t tok = 0;
                 for (int32_t r : sg.rows) tok += L[r];
-                if (folded[si] || sg.rows.size() < 2 || (G <= tkv::kWaveRows && tok * G <= wave_max_rows)) continue;
-                const int64_t tiles = (tok + tpt - 1) / tpt * s.hkv, nb = static_cast<int64_t>(sg.nodes.size());
-                items += (nb + chunk_wide - 1) / chunk_wide * tiles;
-                work += nb * tiles;
-            }
-            if (work > 0 && items < kShortItems) {
-                const int64_t n = (work / (kShortItems - row_items) + 3) / 4 * 4;  // whole 64-key stages
-                const int64_t len = std::min<int64_t>(chunk_wide, std::max<int64_t>(kShortBlocks, n));
-                int64_t slots = n_rows;  // at most as many partials, with the rows' spare ones
-                for (size_t si = 0; si < segs.size(); ++si) {
-                    const Segment& sg = segs[si];
-                    int64_t tok = 0;
-                    for (int32_t r : sg.rows) tok += L[r];
-                    const bool wide = G > tkv::kWaveRows || tok * G > wave_max_rows;
-                    const int64_t most = !wide ? kChunkBlocks : sg.rows.size() < 2 ? chunk_wide : len;
-                    if (!folded[si]) slots += (static_cast<int64_t>(sg.nodes.size()) + most - 1) / most * tok;
+                const bool wide = G > tkv::kWaveRows || tok * G > wave_max_rows;
+                const int64_t nb = static_cast<int64_t>(sg.nodes.size()), most = wide ? chunk_wide : kChunkBlocks;
+                const int64_t n = (nb + most - 1) / most, tiles = (tok + tpt - 1) / tpt * s.hkv;
+                if (wide && sg.rows.size() > 1) {
+                    shared.push_back(Shared{nb, tok, tiles});
+                    items += n * tiles;
+                    work += nb * tiles;
+                    continue;
                 }
-                if (slots * s.hq * (2 * s.d + 4) <= kShortPartialBytes) wide_blocks = static_cast<int32_t>(len);
+                slots += n * tok;
+                if (wide) {
+                    one_row_items += n * tiles;
+                    longest = std::max(longest, std::min(nb, most));
+                }
+            }
+            if (work > 0 && row_items + items < kShortItems) {
+                const bool own_cus = row_items + one_row_items + items <= tkv::kTile8MaxItems;
+                // a cap of whole 64-key stages: an even cut below it takes as many stages as its longest chunk
+                const int64_t n = std::max<int64_t>(own_cus ? longest : kShortBlocks, work / (kShortItems - row_items));
+                const int64_t len = std::min<int64_t>(chunk_wide, (n + 3) / 4 * 4);
+                int64_t all = row_items + one_row_items;
+                for (const Shared& sh : shared) {
+                    const int64_t chunks_of = (sh.nb + len - 1) / len;
+                    slots += chunks_of * sh.tok;
+                    all += chunks_of * sh.tiles;
+                }
+                const bool crowds = own_cus && all > tkv::kTile8MaxItems && 2 * longest > chunk_wide;
+                if (!crowds && slots * s.hq * (2 * s.d + 4) <= kShortPartialBytes) wide_blocks = static_cast<int32_t>(len);
             }
         }
         std::vector<Chunk> chunks;

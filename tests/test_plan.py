@@ -275,3 +275,60 @@ def test_wide_chunks_of_small_plans(blocks, rows, n_items):
     # every chunk's keys are contracted once per KV head, each tile's rows within 128
     assert sum(it[4] for it in wide) == 2 * blocks * -(-rows // 21)
     assert all(it[2] * 6 <= 128 for it in wide)
+
+
+def _candidates(hq, hkv, prompts, rows, q_len, prompt_blocks, tail_blocks, verify=(), **kw):
+    """`rows` rows of q_len tokens under each of `prompts` prompts, each row with blocks of its own; and
+    verify rows of (q_len, blocks) beside them."""
+    import paper_2609_39334_amd as tkv
+    tables, q_lens, nb = [], [], 0
+    for _ in range(prompts):
+        prompt = list(range(nb, nb + prompt_blocks))
+        nb += prompt_blocks
+        for _ in range(rows):
+            tables.append(prompt + list(range(nb, nb + tail_blocks)))
+            q_lens.append(q_len)
+            nb += tail_blocks
+    for n, blocks in verify:
+        tables.append(list(range(nb, nb + blocks)))
+        q_lens.append(n)
+        nb += blocks
+    ki = np.cumsum([0] + [len(t) for t in tables]).astype(np.int32)
+    qi = np.cumsum([0] + q_lens).astype(np.int32)
+    return tkv.Plan((hq, hkv, 128, 16, nb), qi, ki, np.concatenate(tables).astype(np.int32), np.full(nb, 16, np.int32),
+                    upload=False, **kw)
+
+
+@pytest.mark.parametrize("batch,verify,n_items,chunks", [
+    # short verify rows (48 to 56 query rows) and groups of 32 heads: rows' own blocks are tile items too
+    ((28, 4, 2, 15, 8, 64, 4), (), 288, {20, 22}),   # short walks: the prompts set the time
+    ((32, 1, 2, 64, 1, 128, 4), (), 256, {32}),
+    ((32, 1, 1, 8, 1, 65, 4), (), 18, {13}),         # five even chunks (four stages of 64 keys each)
+    ((12, 2, 1, 24, 1, 77, 1), (), 68, {13, 16}),    # (48 wave items among them) four of 16 and the rest
+    ((28, 4, 1, 3, 8, 64, 32), (), 28, {32}),        # no shorter than the rows' own walks
+    ((32, 8, 1, 3, 12, 64, 22), (), 72, {20, 22}),   # (a cap of 24: three even chunks)
+    ((12, 2, 1, 60, 9, 64, 64), (), 172, {64}),      # which are as long as a chunk gets: not cut
+    ((28, 4, 1, 30, 8, 128, 64), (), 232, {64}),
+    ((28, 4, 1, 30, 8, 128, 33), (), 232, {64}),     # 288 in chunks of 43: not worth the 8-wave kernel
+    ((28, 4, 1, 30, 8, 128, 32), (), 288, {42, 43}),
+    ((40, 2, 2, 64, 1, 64, 64), (), 388, {20, 22}),      # more items than CUs already: cut for balance
+    ((12, 2, 1, 24, 1, 64, 1), [(64, 80)], 60, {64}),   # a whole row of 80 blocks beside decode rows
+    ((12, 2, 1, 24, 1, 64, 1), [(64, 20)], 72, {16}),
+])
+def test_short_chunks_beside_other_walks(batch, verify, n_items, chunks):
+    plan, long = _candidates(*batch, verify), _candidates(*batch, verify, options={"wide_chunk_blocks": 64})
+    shared = [it for it in plan.view()["items"] if it[6] == 0 and it[5] < 16 * batch[5]]
+    assert plan.stats["n_items"] == n_items and {int(it[4]) for it in shared} == chunks
+    assert (plan.image() == long.image()) == (chunks == {64})
+    # every chunk's keys are contracted once per tile and KV head
+    tiles = -(-batch[3] * batch[4] // (128 // (batch[0] // batch[1]))) * batch[1] * batch[2]
+    assert sum(it[4] for it in shared) == batch[5] * tiles
+
+
+def test_short_chunks_only_while_the_partials_are_few():
+    # 50 prompts of 64 blocks, one tile item each, are cut shorter; not with tails so long that the plan's
+    # partials (a token's heads x (d fp16 + an fp32 lse) each) would pass 8 MiB
+    few, many = (_candidates(16, 1, 50, 8, 1, 64, tail) for tail in (1, 768))
+    shared = [{it[4] for it in p.view()["items"] if it[6] == 0 and it[2] == 8} for p in (few, many)]
+    assert many.stats["n_slots"] * 16 * 260 > 8 << 20
+    assert max(shared[0]) < 64 and max(shared[1]) == 64
