@@ -7,7 +7,7 @@
 //   O^T += V^T P^T  v_mfma_f32_16x16x32_bf16 over two blocks at a time (A = V^T of both blocks read
 //                   transposed from LDS with ds_read_b64_tr_b16, B = P^T exactly as the two S^T
 //                   results sit in the lanes),
-// (tile items of small batches on v_mfma_f32_32x32x16_bf16, one block at a time: tile_item32)
+// (tile items on v_mfma_f32_32x32x16_bf16 where that is faster, one block at a time: tile_item32)
 // with an online softmax in between (exp2 with the scale folded into one FMA; the exponent base of
 // a row moves only when its maximum grows by more than 2^8, so O is rarely rescaled).  Keys past a
 // block's length are never loaded (row reads are clamped to the block's last token and masked) and
@@ -567,14 +567,9 @@ __device__ __forceinline__ void wave_worker(int w, int lane, const int4* __restr
 // swizzles: the ones below measured zero bank-conflict cycles (SQ_LDS_BANK_CONFLICT) for their own
 // read pattern, whereas one swizzle for both cost 4 cycles per K read (or 2 per V read).  Both depend
 // on r mod 16 only, so a block's rows carry the same pattern wherever the block sits in the stage.
-template <int D>
-__device__ __forceinline__ int tile_swz_k(int r) {
-    return D == 128 ? r & 15 : r & 7;
-}
-template <int D>
-__device__ __forceinline__ int tile_swz_v(int r) {
-    return D == 128 ? (2 * (r & 7)) ^ ((r >> 3) & 1) : r & 7;
-}
+// (These two are for heads of 128: heads of 64 are always tile_item32's.)
+__device__ __forceinline__ int tile_swz_k(int r) { return r & 15; }
+__device__ __forceinline__ int tile_swz_v(int r) { return (2 * (r & 7)) ^ ((r >> 3) & 1); }
 template <int D>
 constexpr int tile_buf_bytes() {
     return 64 * D * 2;
@@ -614,8 +609,8 @@ __device__ __forceinline__ void stage_fetch(const uint16_t* __restrict__ kpool, 
     for (int i = 0; i < 16 / RPI; ++i) {
         const int r = i * RPI + lane / CPR;
         const int row_off = min(r, last) * D * 2;
-        const int koff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_k32<D>(r) : tile_swz_k<D>(r))) * 16);
-        const int voff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_v32<D>(r) : tile_swz_v<D>(r))) * 16);
+        const int koff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_k32<D>(r) : tile_swz_k(r))) * 16);
+        const int voff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_v32<D>(r) : tile_swz_v(r))) * 16);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void_ptr)(kdst + i * 1024), 16, koff, 0, 0, 0);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void_ptr)(vdst + i * 1024), 16, voff, 0, 0, 0);
     }
@@ -631,10 +626,10 @@ __device__ __forceinline__ void stage_barrier() {
 }
 
 // One workgroup of four waves per tile item: a tile of up to 128 query rows (wave w owns rows
-// 32w .. 32w+31 as two column tiles of 16) against the item's key blocks, four blocks per stage.  Stage s+1 is fetched into
-// the other pair of LDS buffers while stage s is contracted; one barrier per stage (a buffer is
-// rewritten only after every wave has passed the barrier that follows its last use).  The stage
-// loop is unrolled by two so that each stage names its buffers statically: the compiler then knows
+// 32w .. 32w+31 as two column tiles of 16) against the item's key blocks, four blocks per stage.
+// Stage s+1 is fetched into the other pair of LDS buffers while stage s is contracted; one barrier per
+// stage (a buffer is rewritten only after every wave has passed the barrier that follows its last use).
+// The stage loop is unrolled by two so that each stage names its buffers statically: the compiler then knows
 // that the reads of one buffer do not depend on the fetch into the other.
 template <int D>
 __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::TokDesc* __restrict__ toks,
@@ -643,6 +638,7 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
                                           uint16_t* __restrict__ o, float* __restrict__ lse, uint16_t* __restrict__ po,
                                           float* __restrict__ plse, int hq, int hkv, int G, float sl2, uint8_t* k0,
                                           uint8_t* v0, uint8_t* k1, uint8_t* v1) {
+    static_assert(D == 128, "the swizzles");
     constexpr int T = 2;
     constexpr int RB = 2 * D;  // bytes per K/V row in the stage buffers
     const int lane = threadIdx.x & 63;
@@ -677,9 +673,9 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
     // chunk 4kk + kg, i.e. koff ^ 64kk.  V, transposed reads: lane (col, kg) reads row
     // 4kg + col/4, bytes 8(col & 3) .. +7 of the 32-byte column run of output tile ct, i.e.
     // voff ^ 32ct.  (The XORs touch only the chunk-index bits of the offsets.)
-    const int koff = col * RB + 16 * (kg ^ tile_swz_k<D>(col));
+    const int koff = col * RB + 16 * (kg ^ tile_swz_k(col));
     const int vrow = 4 * kg + (col >> 2);
-    const int voff = vrow * RB + 16 * (((col & 3) >> 1) ^ tile_swz_v<D>(vrow)) + 8 * (col & 1);
+    const int voff = vrow * RB + 16 * (((col & 3) >> 1) ^ tile_swz_v(vrow)) + 8 * (col & 1);
 
     // block descriptors of a stage: lane l holds block 4s + (l & 3) (the item's last block past its end)
     auto stage_desc = [&](int st) { return bd[min(4 * st + (lane & 3), nb - 1)]; };
@@ -1099,14 +1095,8 @@ __device__ __forceinline__ void tile_item32(const tkv::ItemDesc& it, const tkv::
 // the kinds with period 2 per XCD, which locks each kind onto two of the four engines.)  Then come
 // the remaining tile items, then the remaining wave-grid workgroups.  Either way tile item i and
 // wave workgroup j run on XCDs i % 8 and j % 8, as the planner assumed.
-// W32: the tile items run on v_mfma_f32_32x32x16_bf16 (tile_item32) or 16x16x32 (tile_item).  The larger
-// instruction takes half the issue slots: 5% fewer cycles on every plan measured.  But it reads and writes
-// the accumulators twice as often per flop, and where tiles keep the whole chip busy for long the power
-// limit sets the time: eight queries' step verification (4,000 tile items) ran 1.72 M cycles at 1.97 GHz
-// with 16x16x32, 1.64 M at 1.82 GHz with 32x32x16.  So plans of up to kTile32MaxItems tile items (two
-// rounds of the chip's workgroup slots, the second mostly a tail) take 32x32x16: 1,632 candidates under
-// eight prompts (720 items) 65.0 -> 62.0 us, the speculative tree 102.7 -> 101.1 us; larger ones keep
-// 16x16x32 (step verification 780 against 816 us, the serving batch 4.31 against 4.43 ms).
+// W32: the tile items run on v_mfma_f32_32x32x16_bf16 (tile_item32) or 16x16x32 (tile_item); the plan says
+// which (tkv_plan::tile32), by how many items it has and how far they walk.
 template <int D, bool W32>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd(
     const tkv::ItemDesc* __restrict__ items, int n_tile, int n_wave_wg, int runs, const tkv::TokDesc* __restrict__ toks,
@@ -1465,7 +1455,7 @@ static int launch_d(const tkv_plan* p, uint8_t* ws, const void* q, const void* k
                               static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,
                               p->group, sl2);
     else if (grid > 0)
-        hipExtLaunchKernelGGL((n_tile <= kTile32MaxItems ? attn_fwd<D, true> : attn_fwd<D, false>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, st,
+        hipExtLaunchKernelGGL((D == 64 || p->tile32 ? attn_fwd<D, true> : attn_fwd<D, D == 64>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, st,
                               ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, 0, items, n_tile, n_wave_wg, runs, toks, blks,
                               wdesc, woff, wtiles, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                               static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,

@@ -36,7 +36,6 @@ constexpr int kWaveWorkers = 2048;  // waves of the wave kernel: 2 workgroups of
 constexpr int kWaveWG = 4;      // waves per workgroup of the wave kernel (independent; no barriers)
 constexpr int kTile8MaxItems = 256;  // tile items (and no wave grid) up to which 8-wave workgroups run them: one per CU
 constexpr int kTileRowsSmall = 64;   // rows of a tile of a batch so small that the chip has a CU for every such tile
-constexpr int kTile32MaxItems = 1024;  // tile items up to which attn_fwd contracts them with 32x32x16 MFMAs (two rounds of the slots)
 constexpr int kInterleaveRun = 32;   // workgroups per run when tile items and wave-grid workgroups alternate:
                                      // 8 XCDs x 4 shader engines, one workgroup of a kind per engine
 constexpr int32_t kNoLimit = 1 << 30;  // causal limit of a q_len-1 token: it sees its whole path (kv_len <= 2^30)
@@ -135,6 +134,7 @@ struct tkv_plan {
     std::vector<int32_t> wave_tiles;          // [n_waves] column tiles of the wave's items (0: no work)
     int32_t n_slots = 0;
     int32_t tile_rows = 0;  // query rows of a tile item: kTileRowsWG, or kTileRowsSmall (tile8 plans only)
+    bool tile32 = false;  // attn_fwd contracts its tile items with 32x32x16 MFMAs, not 16x16x32
     bool tile8 = false;  // tile items only, few enough to run as 8-wave workgroups (kTile8MaxItems)
     // workspace layout (byte offsets)
     size_t off_items = 0, off_toks = 0, off_blks = 0, off_merges = 0, off_mslots = 0, off_wdesc = 0, off_woff = 0, off_wtiles = 0;

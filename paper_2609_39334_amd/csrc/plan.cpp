@@ -218,6 +218,86 @@ void tile_full(int32_t n, int32_t cap, F f) {
     for (int32_t a = 0; a < n; a += cap) f(a, std::min(n, a + cap));
 }
 
+// The longest key run of a shared chunk on the tiles, chunk_wide or less.  Shared segments on the tiles of a
+// batch where they and the whole rows make few tile items are cut shorter, into about kShortItems such items:
+// each takes a CU, and walks its keys in a shorter time.  Where every tile item has a CU of its own, the
+// longest walk that stays as it is (a whole row's, a one-row segment's) sets the call's time: no chunk is cut
+// shorter than that, and a cut that gives the plan more items than CUs has to be worth half a long chunk's
+// walk.
+__attribute__((noinline)) int32_t shared_chunk_blocks(const tkv_shape& s, int32_t n_rows, const std::vector<int32_t>& L,
+                                                      const std::vector<int32_t>& row_len, const std::vector<Segment>& segs,
+                                                      const std::vector<uint8_t>& folded, int32_t tpt,
+                                                      int64_t wave_max_rows, int32_t chunk_wide) {
+    const int32_t G = s.hq / s.hkv;
+    int64_t one_row_items = 0, items = 0, work = 0;  // work: the shared ones' key blocks x tiles x KV heads
+    int64_t longest = kShortBlocks;
+    int64_t slots = n_rows;  // at most as many partials besides the shared tile segments', with the rows' spare ones
+    struct Shared {
+        int64_t nb, tok, tiles;
+    };
+    std::vector<Shared> shared;
+    for (size_t si = 0; si < segs.size(); ++si) {
+        if (folded[si]) continue;
+        const Segment& sg = segs[si];
+        int64_t tok = 0;
+        for (int32_t r : sg.rows) tok += L[r];
+        const bool wide = G > tkv::kWaveRows || tok * G > wave_max_rows;
+        const int64_t nb = static_cast<int64_t>(sg.nodes.size()), most = wide ? chunk_wide : kChunkBlocks;
+        const int64_t n = (nb + most - 1) / most, tiles = (tok + tpt - 1) / tpt * s.hkv;
+        if (wide && sg.rows.size() > 1) {
+            shared.push_back(Shared{nb, tok, tiles});
+            items += n * tiles;
+            work += nb * tiles;
+            continue;
+        }
+        slots += n * tok;
+        if (wide) {
+            one_row_items += n * tiles;
+            longest = std::max(longest, std::min(nb, most));
+        }
+    }
+    if (work == 0 || items >= kShortItems) return chunk_wide;
+    int64_t row_items = 0;
+    for (int32_t r = 0; r < n_rows; ++r)
+        if (static_cast<int64_t>(L[r]) * G >= tkv::kTileRows) {
+            row_items += static_cast<int64_t>((L[r] + tpt - 1) / tpt) * s.hkv;
+            longest = std::max<int64_t>(longest, row_len[r]);
+        }
+    if (row_items + items >= kShortItems) return chunk_wide;
+    const bool own_cus = row_items + one_row_items + items <= tkv::kTile8MaxItems;
+    // a cap of whole 64-key stages: an even cut below it takes as many stages as its longest chunk
+    const int64_t n = std::max<int64_t>(own_cus ? longest : kShortBlocks, work / (kShortItems - row_items));
+    const int64_t len = std::min<int64_t>(chunk_wide, (n + 3) / 4 * 4);
+    int64_t all = row_items + one_row_items;
+    for (const Shared& sh : shared) {
+        const int64_t chunks = (sh.nb + len - 1) / len;
+        slots += chunks * sh.tok;
+        all += chunks * sh.tiles;
+    }
+    const bool crowds = own_cus && all > tkv::kTile8MaxItems && 2 * longest > chunk_wide;
+    if (crowds || slots * s.hq * (2 * s.d + 4) > kShortPartialBytes) return chunk_wide;
+    return static_cast<int32_t>(len);
+}
+
+// Whether attn_fwd contracts the tile items with 32x32x16 MFMAs.  They take half the issue slots of 16x16x32
+// but move the accumulators twice as often per flop, and are the faster ones until long walks keep the whole
+// chip busy and the clock falls.  So the line is on the stages (64 keys) that an item walks on average, by
+// the number of items.  Time with 16x16x32 over that with 32x32x16, verify batches of 28/4, 32/8 and 12/2
+// heads of 128:
+//   items         4 stages   8          11         14-18       20-24       28-38       67 and more
+//   to 384        1.16       1.08-1.09  1.06       1.02-1.05   1.02-1.04   1.00-1.03   1.01-1.02
+//   to 768        1.09-1.20  1.06-1.10  1.02-1.11  1.00-1.07   0.98-1.03   0.98-1.02   0.94-1.00
+//   1,000-2,224   1.09-1.12  1.05-1.06  1.00-1.06  0.99-1.01   0.98-1.00   0.96-0.99   0.93-0.98
+//   4,400-8,048   1.11-1.13  1.01-1.03  1.00       0.95-0.99   0.94-0.98   0.96-0.98   0.94-0.95
+// Heads of 64 halve the accumulators: 1.00-1.07 at every size measured (480 to 16,000 items, 11 to 510 stages).
+__attribute__((noinline)) bool takes_mfma32(int32_t d, const std::vector<ItemDesc>& items) {
+    const int64_t n = static_cast<int64_t>(items.size());
+    if (d == 64 || n <= 384) return true;
+    int64_t stages = 0;
+    for (const ItemDesc& it : items) stages += (it.n_blk + 3) >> 2;
+    return stages <= n * (n <= 768 ? 24 : n <= 2048 ? 16 : 8);
+}
+
 // The planner's working arrays, kept per thread from one plan to the next (a loop that plans every
 // step then fills memory it already holds).
 struct Scratch {
@@ -265,6 +345,7 @@ void clear_plan(tkv_plan* p) {
     p->wave_tiles.clear();
     p->n_slots = 0;
     p->tile_rows = 0;
+    p->tile32 = false;
     p->tile8 = false;
     p->off_items = p->off_toks = p->off_blks = p->off_merges = p->off_mslots = p->off_wdesc = p->off_woff = p->off_wtiles = 0;
     p->off_po = p->off_plse = p->desc_bytes = p->total_bytes = 0;
@@ -589,60 +670,9 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
                 folded[p] = 1;
             }
         }
-        // Shared segments on the tiles of a batch where they and the whole rows make few tile items are cut
-        // shorter, into about kShortItems such items: each takes a CU, and walks its keys in a shorter time.
-        // Where every tile item has a CU of its own, the longest walk that stays as it is (a whole row's, a
-        // one-row segment's) sets the call's time: no chunk is cut shorter than that, and a cut that gives
-        // the plan more items than CUs has to be worth half a long chunk's walk.
-        int32_t wide_blocks = chunk_wide;
-        if (!opts || opts->wide_chunk_blocks < 0) {
-            int64_t row_items = 0, one_row_items = 0, items = 0, work = 0;  // work: the shared ones' key blocks x tiles x KV heads
-            int64_t longest = kShortBlocks;
-            int64_t slots = n_rows;  // at most as many partials besides the shared tile segments', with the rows' spare ones
-            for (int32_t r = 0; r < n_rows; ++r)
-                if (static_cast<int64_t>(L[r]) * G >= tkv::kTileRows) {
-                    row_items += static_cast<int64_t>((L[r] + tpt - 1) / tpt) * s.hkv;
-                    longest = std::max<int64_t>(longest, in.row_len[r]);
-                }
-            struct Shared {
-                int64_t nb, tok, tiles;
-            };
-            std::vector<Shared> shared;
-            for (size_t si = 0; si < segs.size(); ++si) {
-                if (folded[si]) continue;
-                const Segment& sg = segs[si];
-                int64_t tok = 0;
-                for (int32_t r : sg.rows) tok += L[r];
-                const bool wide = G > tkv::kWaveRows || tok * G > wave_max_rows;
-                const int64_t nb = static_cast<int64_t>(sg.nodes.size()), most = wide ? chunk_wide : kChunkBlocks;
-                const int64_t n = (nb + most - 1) / most, tiles = (tok + tpt - 1) / tpt * s.hkv;
-                if (wide && sg.rows.size() > 1) {
-                    shared.push_back(Shared{nb, tok, tiles});
-                    items += n * tiles;
-                    work += nb * tiles;
-                    continue;
-                }
-                slots += n * tok;
-                if (wide) {
-                    one_row_items += n * tiles;
-                    longest = std::max(longest, std::min(nb, most));
-                }
-            }
-            if (work > 0 && row_items + items < kShortItems) {
-                const bool own_cus = row_items + one_row_items + items <= tkv::kTile8MaxItems;
-                // a cap of whole 64-key stages: an even cut below it takes as many stages as its longest chunk
-                const int64_t n = std::max<int64_t>(own_cus ? longest : kShortBlocks, work / (kShortItems - row_items));
-                const int64_t len = std::min<int64_t>(chunk_wide, (n + 3) / 4 * 4);
-                int64_t all = row_items + one_row_items;
-                for (const Shared& sh : shared) {
-                    const int64_t chunks_of = (sh.nb + len - 1) / len;
-                    slots += chunks_of * sh.tok;
-                    all += chunks_of * sh.tiles;
-                }
-                const bool crowds = own_cus && all > tkv::kTile8MaxItems && 2 * longest > chunk_wide;
-                if (!crowds && slots * s.hq * (2 * s.d + 4) <= kShortPartialBytes) wide_blocks = static_cast<int32_t>(len);
-            }
-        }
+        int32_t wide_blocks = chunk_wide;  // longest key run of a shared chunk on the tiles
+        if (!segs.empty() && (!opts || opts->wide_chunk_blocks < 0))
+            wide_blocks = shared_chunk_blocks(s, n_rows, L, in.row_len, segs, folded, tpt, wave_max_rows, chunk_wide);
         std::vector<Chunk> chunks;
         std::vector<BlkDesc>& seg_blks = sc.seg_blks;  // each segment's key blocks, in path order
         seg_blks.clear();
@@ -1008,6 +1038,7 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         // a plan of a few tile items and nothing else gives each tile a CU to itself: eight waves then
         // share the tile's rows and keys, which shortens its walk
         p->tile8 = p->wave_items.empty() && !p->items.empty() && static_cast<int64_t>(p->items.size()) <= tile8_max;
+        p->tile32 = takes_mfma32(s.d, p->items);
         st.n_slots = p->n_slots;
         st.n_merge = static_cast<int32_t>(p->merges.size());
 
@@ -1264,6 +1295,7 @@ void swap_contents(tkv_plan* a, tkv_plan* b) {
     swap(a->wave_tiles, b->wave_tiles);
     swap(a->n_slots, b->n_slots);
     swap(a->tile_rows, b->tile_rows);
+    swap(a->tile32, b->tile32);
     swap(a->tile8, b->tile8);
     swap(a->off_items, b->off_items);
     swap(a->off_toks, b->off_toks);

@@ -345,3 +345,28 @@ def test_verify_tile_variants_at_their_edges(hq, hkv, d, tokens):
     variant = 0 if small <= 256 else 1 if full <= 256 else 2 if full <= 1024 else 3
     assert variant == {(300, 7): 0, (750, 7): 1, (2000, 7): 2, (5200, 7): 3,
                        (300, 4): 0, (750, 4): 0, (2000, 4): 2, (5200, 4): 2}[(tokens, g)]
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (15, 5, 128), (16, 4, 64)])
+@pytest.mark.parametrize("n_items,ctx,wide", [(350, (1500, 1800), True), (400, (900, 1200), True), (400, (1500, 1800), False)])
+def test_verify_tiles_by_walk_length(hq, hkv, d, n_items, ctx, wide):
+    # 4-wave tile items on either side of the matrix instructions' line: 32x32x16 for heads of 128 up to 384
+    # items or where the walks are short (24 stages of four blocks on average), always for heads of 64
+    g = hq // hkv
+    wl = W.Workload(f"tile_walks_{n_items}", W.Shape(hq, hkv, d), 51, note="verify-only batch")
+    rt = np.random.default_rng([51, n_items])
+    lengths = [n for n in (10, 17, 33, 64, 65, 100, 130, 257) if n * g >= 64]
+    roots = [wl.extend(-1, rt.integers(0, 32000, int(n)), True) for n in np.linspace(*ctx, 4)]
+    cands, tiles = [], []
+    while sum(tiles) < n_items:
+        n = lengths[len(cands) % len(lengths)]
+        cands.append((wl.extend(roots[len(cands) % 4], rt.integers(0, 32000, n), True), n))
+        tiles.append(-(-n // (128 // g)) * hkv)
+    for c in roots:
+        wl.prune(c)
+    wl.launch("verify", cands)
+    wl.finalize()
+    b, st = compare(wl, 0, options={"tile8_max_items": 0})
+    stages = sum(t * -(-len(table) // 4) for t, table in zip(tiles, b.tables))
+    assert st["n_items_wave"] == 0 and st["n_items"] == sum(tiles)
+    assert (sum(tiles) <= 384 or stages <= 24 * sum(tiles)) == wide
