@@ -100,6 +100,8 @@ struct PlanInputs {
     std::vector<int32_t> tail_run;   // [n_rows] wblks run (index / kWaveBlocks) of the tail chunk, or -1
     std::vector<int32_t> spare;      // [n_rows] 1: the token's partial range ends in an unused slot
     std::vector<int32_t> merge_of;   // [n_rows] the token's MergeDesc, or -1
+    int64_t chunk_room = INT64_MAX;  // chunks that tails may open while a plan made from scratch would cut its
+                                     // shared segments as this one did
     // built on the first in-place update
     bool indexed = false;
     std::vector<int32_t> owner;      // [num_blocks] the one row whose table holds the block, -1 none, -2 several

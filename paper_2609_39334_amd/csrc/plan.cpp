@@ -223,11 +223,11 @@ void tile_full(int32_t n, int32_t cap, F f) {
 // each takes a CU, and walks its keys in a shorter time.  Where every tile item has a CU of its own, the
 // longest walk that stays as it is (a whole row's, a one-row segment's) sets the call's time: no chunk is cut
 // shorter than that, and a cut that gives the plan more items than CUs has to be worth half a long chunk's
-// walk.
+// walk.  room: how many more partials there may be before the segments would no longer be cut.
 __attribute__((noinline)) int32_t shared_chunk_blocks(const tkv_shape& s, int32_t n_rows, const std::vector<int32_t>& L,
                                                       const std::vector<int32_t>& row_len, const std::vector<Segment>& segs,
                                                       const std::vector<uint8_t>& folded, int32_t tpt,
-                                                      int64_t wave_max_rows, int32_t chunk_wide) {
+                                                      int64_t wave_max_rows, int32_t chunk_wide, int64_t* room) {
     const int32_t G = s.hq / s.hkv;
     int64_t one_row_items = 0, items = 0, work = 0;  // work: the shared ones' key blocks x tiles x KV heads
     int64_t longest = kShortBlocks;
@@ -275,7 +275,9 @@ __attribute__((noinline)) int32_t shared_chunk_blocks(const tkv_shape& s, int32_
         all += chunks * sh.tiles;
     }
     const bool crowds = own_cus && all > tkv::kTile8MaxItems && 2 * longest > chunk_wide;
-    if (crowds || slots * s.hq * (2 * s.d + 4) > kShortPartialBytes) return chunk_wide;
+    const int64_t most_slots = kShortPartialBytes / (static_cast<int64_t>(s.hq) * (2 * s.d + 4));
+    if (crowds || slots > most_slots) return chunk_wide;
+    *room = most_slots - slots;
     return static_cast<int32_t>(len);
 }
 
@@ -495,6 +497,7 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         in.tail_run.assign(n_rows, -1);
         in.spare.assign(n_rows, 0);
         in.merge_of.assign(n_rows, -1);
+        in.chunk_room = INT64_MAX;
         tkv_plan_stats& st = p->stats;
         st.n_rows = n_rows;
         st.n_qtok = n_rows ? q_indptr[n_rows] : 0;
@@ -672,7 +675,8 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         }
         int32_t wide_blocks = chunk_wide;  // longest key run of a shared chunk on the tiles
         if (!segs.empty() && (!opts || opts->wide_chunk_blocks < 0))
-            wide_blocks = shared_chunk_blocks(s, n_rows, L, in.row_len, segs, folded, tpt, wave_max_rows, chunk_wide);
+            wide_blocks = shared_chunk_blocks(s, n_rows, L, in.row_len, segs, folded, tpt, wave_max_rows, chunk_wide,
+                                              &in.chunk_room);
         std::vector<Chunk> chunks;
         std::vector<BlkDesc>& seg_blks = sc.seg_blks;  // each segment's key blocks, in path order
         seg_blks.clear();
@@ -1421,7 +1425,7 @@ TKV_EXPORT int tkv_plan_update(tkv_plan* p, const int32_t* kv_indptr, const int3
                 n_open += 1;
             }
         }
-        if (n_open * hkv > in.free_waves.size()) fits = false;
+        if (n_open * hkv > in.free_waves.size() || static_cast<int64_t>(n_open) > in.chunk_room) fits = false;
         for (int32_t b = 0; b < s.num_blocks && fits; ++b) {
             if (block_len[b] == in.block_len[b]) continue;
             const int32_t o = in.owner[b];
@@ -1460,6 +1464,7 @@ TKV_EXPORT int tkv_plan_update(tkv_plan* p, const int32_t* kv_indptr, const int3
     }
 
     // ------------------------------------------------ in place
+    if (in.chunk_room != INT64_MAX) in.chunk_room -= static_cast<int64_t>(n_open);
     uint8_t* img = p->image.get();
     auto record = [&](int32_t item) {
         return reinterpret_cast<int32_t*>(img + p->off_wdesc + static_cast<size_t>(in.rec_of[item]) * sizeof(tkv::WaveDesc));

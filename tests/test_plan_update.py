@@ -297,3 +297,33 @@ def test_update_of_an_empty_plan():
     plan = tkv.Plan((8, 2, 64, 16, 4), [0], [0], [], [16, 3, 0, 0], upload=False)
     assert plan.update([0], [], [16, 4, 0, 0])
     assert plan.stats["n_items"] == 0
+
+
+def test_update_keeps_a_fresh_plans_chunk_length():
+    # a plan cuts its shared segment short while its partials stay within 8 MiB (992 slots of 64 heads of 64):
+    # tails that open chunks past that leave the in-place path, since a plan from scratch would not be cut
+    hq, hkv, d, rows, prompt = 64, 4, 64, 24, 64
+    tails = [16 * 36 + (16 if r < 6 else 0) for r in range(rows)]      # 990 slots with the spare ones
+    tables, nb = [], prompt
+    for t in tails:
+        tables.append(list(range(prompt)) + list(range(nb, nb + t)))
+        nb += t
+    dims = (hq, hkv, d, 16, nb + 8)
+    bl = np.full(nb + 8, 16, np.int32)
+    qi = np.arange(rows + 1, dtype=np.int32)
+
+    def arrays():
+        return np.cumsum([0] + [len(t) for t in tables]).astype(np.int32), np.concatenate(tables).astype(np.int32)
+
+    def shared(p):
+        return sorted(int(it[4]) for it in p.view()["items"] if it[6] == 0 and it[5] < 16 * prompt)
+
+    plan = tkv.Plan(dims, qi, *arrays(), bl, upload=False)
+    assert set(shared(plan)) == {16}
+    for r, in_place in ((7, True), (8, True), (9, False)):
+        tables[r].append(nb)
+        nb += 1
+        assert tkv.tkv_plan_update(plan.h, *arrays(), bl) is in_place
+        fresh = tkv.Plan(dims, qi, *arrays(), bl, upload=False)
+        assert shared(plan) == shared(fresh) and plan.stats["n_items"] == fresh.stats["n_items"]
+    assert set(shared(plan)) == {64}
