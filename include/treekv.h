@@ -235,9 +235,11 @@ size_t tkv_plan_workspace_bytes(const tkv_plan* plan);
  * for it before the plan's host memory changes or is recycled (tkv_plan_update, the next upload,
  * tkv_plan_destroy), so a plan may be updated or destroyed right after an upload; those calls may
  * then wait for the work enqueued on hip_stream before the copy.  Descriptors of up to 256 KiB
- * usually pass through one of four pinned slots per GPU (1 MiB, held until the process ends) and
- * need no such wait; under stream capture, or with every slot in flight, they are copied from the
- * plan as larger ones are.  EINVAL (size, alignment, NULL), EHIP. */
+ * usually pass through one of four pinned slots per GPU (1 MiB, made by the first upload, held until
+ * the process ends) and need no such wait; under stream capture, or with every slot in flight, they
+ * are copied from the plan as larger ones are (a graph that captured an upload copies from the plan
+ * at every launch).  An upload does not disturb a capture on another stream.  EINVAL (size,
+ * alignment, NULL), EHIP. */
 int tkv_plan_upload(tkv_plan* plan, void* d_workspace, size_t bytes, void* hip_stream);
 
 void tkv_plan_destroy(tkv_plan* plan);

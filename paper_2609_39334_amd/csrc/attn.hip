@@ -1262,7 +1262,7 @@ struct StageSlot {
 };
 struct StagePool {
     std::mutex m;
-    bool tried[kMaxDevices] = {};
+    bool made[kMaxDevices] = {};  // the first slot is there (while it cannot be had, every upload tries again)
     StageSlot slots[kMaxDevices][kStageSlots];
 };
 StagePool& stage_pool() {
@@ -1270,22 +1270,42 @@ StagePool& stage_pool() {
     return *pool;
 }
 
+// While another stream is captured in global mode, a thread in that mode may make no call that could be unsafe
+// then (allocations, event queries): they are refused, and end that capture.  None of the calls made for the
+// slots touches a stream, so this thread makes them in relaxed mode.
+class RelaxedCapture {
+  public:
+    RelaxedCapture() { swapped_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
+    ~RelaxedCapture() {
+        if (swapped_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+    }
+
+  private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+    bool swapped_ = false;
+};
+
 StageSlot* take_stage() {
+    const RelaxedCapture relaxed;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
     StagePool& pool = stage_pool();
     std::lock_guard<std::mutex> lock(pool.m);
     StageSlot* slots = pool.slots[dev];
-    if (!pool.tried[dev]) {
-        pool.tried[dev] = true;
+    if (!pool.made[dev]) {
         for (int i = 0; i < kStageSlots; ++i) {
-            if (hipHostMalloc(&slots[i].host, kStageBytes, hipHostMallocDefault) != hipSuccess ||
-                hipEventCreateWithFlags(&slots[i].done, hipEventDisableTiming) != hipSuccess) {
+            if (hipHostMalloc(&slots[i].host, kStageBytes, hipHostMallocDefault) != hipSuccess) {
                 (void)hipGetLastError();  // not an error of the upload: it copies from the image
-                if (slots[i].host) (void)hipHostFree(slots[i].host);
                 slots[i].host = nullptr;
                 break;
             }
+            if (hipEventCreateWithFlags(&slots[i].done, hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                (void)hipHostFree(slots[i].host);
+                slots[i].host = nullptr;
+                break;
+            }
+            pool.made[dev] = true;
         }
     }
     for (int i = 0; i < kStageSlots; ++i) {

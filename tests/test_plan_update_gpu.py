@@ -146,3 +146,83 @@ def test_many_uploads_in_flight(rows):
     for img, ws in made[0] + made[1]:
         assert (len(img) <= 256 << 10) == (rows == 5)
         assert ws[:len(img)].cpu().numpy().tobytes() == img
+
+
+BESIDE_A_CAPTURE = """
+import numpy as np, torch
+import paper_2609_39334_amd as tkv
+rows = 6
+tables = np.concatenate([np.r_[0:8, 8 + 3 * r:11 + 3 * r] for r in range(rows)]).astype(np.int32)
+ptr = np.arange(rows + 1, dtype=np.int32)
+
+def plan():
+    h = tkv.tkv_plan_create((12, 2, 128, 16, 8 + 3 * rows), ptr, 11 * ptr, tables, np.full(8 + 3 * rows, 16, np.int32))
+    return h, torch.zeros(tkv.tkv_plan_workspace_bytes(h), dtype=torch.uint8, device="cuda"), tkv.tkv_plan_image(h)[0]
+
+side, main = torch.cuda.Stream(), torch.cuda.Stream()
+x = torch.ones(1 << 20, device="cuda")
+y = torch.zeros_like(x)
+plans = [plan() for _ in range(3)]
+busy = torch.zeros(256 << 20, dtype=torch.uint8, device="cuda")
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph, stream=main, capture_error_mode="global"):
+    y.copy_(x * 2)
+    for h, ws, _ in plans[:2]:                       # the process's first uploads, on another stream
+        tkv.tkv_plan_upload(h, ws, side.cuda_stream)
+    y.add_(1)
+torch.cuda.synchronize()
+assert all(ws[:len(img)].cpu().numpy().tobytes() == img for _, ws, img in plans[:2])
+graph.replay()
+torch.cuda.synchronize()
+assert bool((y == 3).all())
+h, ws, img = plans[2]
+with torch.cuda.stream(side):
+    for _ in range(300):
+        busy.add_(1)
+tkv.tkv_plan_upload(h, ws, side.cuda_stream)
+tkv.tkv_plan_destroy(h)
+assert not side.query()                              # through a slot: destroying the plan waits for nothing
+side.synchronize()
+assert ws[:len(img)].cpu().numpy().tobytes() == img
+print("OK")
+"""
+
+
+def test_upload_beside_a_capture():
+    # the first upload makes the pinned slots, and looks at them in every later one, while another stream is
+    # captured in global mode: the capture goes on, and the slots serve the uploads after it
+    import os
+    import subprocess
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-c", BESIDE_A_CAPTURE], cwd=root, capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0 and run.stdout.strip().endswith("OK"), run.stdout + run.stderr
+
+
+def test_upload_under_capture():
+    # the graph copies the plan's descriptors at every launch, whatever the workspace held before
+    import paper_2609_39334_amd as tkv
+    tree = DecodeTree(25, W.Shape(12, 2, 128), [3, 70, 255, 256, 31], num_blocks=2048)
+    _, ki, kb, bl = tree.tables()
+    n = int(sum(tree.q_lens))
+    q = torch.randn((n, 12, 128), device="cuda").bfloat16()
+    k, v = (torch.randn((tree.num_blocks, 2, 16, 128), device="cuda").bfloat16() for _ in "kv")
+    o, lse = torch.empty_like(q), torch.empty((n, 12), device="cuda")
+    ref = tkv.Plan(tree.dims(), tree.q_indptr(), ki, kb, bl)
+    (ref.decode if max(tree.q_lens) == 1 else ref.verify)(q, k, v, o, lse)
+    want = o.clone(), lse.clone()
+    plan = tkv.Plan(tree.dims(), tree.q_indptr(), ki, kb, bl, upload=False)
+    ws = torch.empty(tkv.tkv_plan_workspace_bytes(plan.h), dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        tkv.tkv_plan_upload(plan.h, ws, stream.cuda_stream)
+        (plan.decode if max(tree.q_lens) == 1 else plan.verify)(q, k, v, o, lse, stream)
+    for _ in range(4):
+        ws.zero_()
+        o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, want[0]) and torch.equal(lse, want[1])
