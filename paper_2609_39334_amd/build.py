@@ -24,12 +24,12 @@ HOST_FLAGS = ["-std=c++17", "-O2", "-fPIC", "-fvisibility=hidden", "-Wall", "-We
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-std=c++17", "-O3", "-fPIC", "-fvisibility=hidden",
     "-mcode-object-version=5",
-    # no NaN ever enters the arithmetic (masked scores are -inf, guarded where they could meet), so the
-    # compiler need not quiet the inputs of every max
-    "-fno-honor-nans",
     # no packed-fp32 instructions in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+# attention and sampling: masked scores are -inf, guarded where they could meet, and no NaN enters the
+# arithmetic, so the compiler need not quiet the inputs of every max.  (Activations may hold NaN.)
+FILE_FLAGS = {"attn.hip": ["-fno-honor-nans"], "cd_sample.hip": ["-fno-honor-nans"]}
 
 
 def _run_all(cmds, verbose):
@@ -60,7 +60,7 @@ def build(verbose: bool = False, extra_host_flags=()) -> str:
         objs.append(o)
     for s in HIP_SOURCES:
         o = os.path.join(OUT, s + ".o")
-        cmds.append([HIPCC, *HIP_FLAGS, *inc, "-c", os.path.join(CSRC, s), "-o", o])
+        cmds.append([HIPCC, *HIP_FLAGS, *FILE_FLAGS.get(s, []), *inc, "-c", os.path.join(CSRC, s), "-o", o])
         objs.append(o)
     _run_all(cmds, verbose)
     tmp = LIB + ".tmp"

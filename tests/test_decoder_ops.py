@@ -85,6 +85,54 @@ def test_swiglu(rows, inter):
     _close(out, ref, ref.abs() + 2.0 ** -100)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [512, 511])
+def test_infinities_and_nan_as_the_tensor_operations_give_them(n):
+    # a row each with +inf, -inf and NaN among its values, and one without; both forms of the row kernels
+    inf, nan = float("inf"), float("nan")
+    g = _gen(n)
+    odd = [(0, inf), (1, -inf), (2, nan)]
+
+    def same(got, ref):
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+        ok = ref.isfinite()
+        _close(got[ok], ref[ok].double(), ref[ok].double().abs() + 2.0 ** -100)
+        assert torch.equal(got[ref.isinf()].sign(), ref[ref.isinf()].sign())
+
+    gu = (_randn(g, 4, 2 * n) * 3).bfloat16()
+    for r, x in odd:
+        gu[r, 5], gu[r, n + 7], gu[r, 9], gu[r, n + 9] = x, x, x, 0.0
+    gf = gu.float()
+    same(tkv.tkv_swiglu(gu), (torch.nn.functional.silu(gf[:, :n]) * gf[:, n:]).bfloat16())
+
+    w = torch.rand(n, generator=g, device="cuda") + 0.5
+    for with_delta in (False, True):
+        x = _randn(g, 4, n)
+        delta = _randn(g, 4, n).bfloat16() if with_delta else None
+        for r, bad in odd:
+            (delta if with_delta else x)[r, 5] = bad
+        want = x + delta.float() if with_delta else x.clone()
+        h = tkv.tkv_add_rmsnorm(x, delta, w, 1e-6)
+        assert torch.equal(x.isnan(), want.isnan()) and torch.equal(x.nan_to_num(), want.nan_to_num())
+        same(h, (want * torch.rsqrt((want * want).mean(-1, keepdim=True) + 1e-6) * w).bfloat16())
+
+    d, hq, hkv = 64, 2, 1
+    qkv = _randn(g, 4, (hq + 2 * hkv) * d).bfloat16()
+    for r, bad in odd:
+        qkv[r, 3], qkv[r, 2 * d + 40], qkv[r, 3 * d + 1] = bad, bad, bad
+    ang = torch.rand((4, d // 2), generator=g, device="cuda") * 100
+    cos, sin = torch.cos(ang), torch.sin(ang)
+    k, v = (torch.zeros((4, hkv, 16, d), device="cuda").bfloat16() for _ in "kv")
+    dst = torch.arange(4, device="cuda", dtype=torch.int32) * 16
+    q = tkv.tkv_rope_append(qkv, cos, sin, dst, hq, k, v)
+    heads = qkv.view(4, -1, d).float()
+    a, b = heads[:, :hq + hkv, :d // 2], heads[:, :hq + hkv, d // 2:]
+    c, s = cos[:, None], sin[:, None]
+    rot = torch.cat((a * c - b * s, b * c + a * s), -1).bfloat16()
+    for got, ref in ((q, rot[:, :hq]), (k[:, :, 0], rot[:, hq:]), (v[:, :, 0], heads[:, hq + hkv:].bfloat16())):
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+
+
 def test_bad_arguments_are_refused():
     # refused before any device access (no GPU needed)
     L = tkv.lib()
