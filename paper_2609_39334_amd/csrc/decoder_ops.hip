@@ -35,7 +35,7 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// One workgroup per row.  Rows of up to 8,192 (a multiple of four) stay in registers between the sum of
+// One workgroup per row.  Rows of up to 8,192 (a multiple of eight) stay in registers between the sum of
 // squares and the scaling; other rows are read again (from the caches: the thread has just written them).
 template <bool HELD>
 __global__ __launch_bounds__(kThreads) void add_rmsnorm(int hidden, float eps, float* __restrict__ x,
@@ -139,8 +139,18 @@ __global__ __launch_bounds__(kThreads) void rope_append(int64_t n_pieces, int hq
     *reinterpret_cast<uint4*>(out + D / 2 + 8 * c) = ob;
 }
 
+// SiLU(g) u = g / (1 + exp(-g)) u.  exp(-g) is 2^n 2^f: g has the 8 significant bits of bf16 and kHi 13, so
+// g kHi is exact, n its nearest integer, and f rounds once.  For negative g the reciprocal is taken of 2^-64 of
+// the sum, so that nothing is flushed while exp(-g) is finite (exp2 and rcp of the plain values gave 0 for
+// gates under -87).  The same bf16 results as with expf and a division on 2 M values.  813 rows of 18,944:
+// 16.7 us, 18.1 us with those, 16.3 us with plain exp2 and rcp.
 __device__ __forceinline__ float silu_mul(float g, float u) {
-    return g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
+    constexpr float kHi = 0x1.715p0f, kLo = static_cast<float>(1.4426950408889634 - 0x1.715p0);  // log2(e)
+    const float a = fminf(fmaxf(-kHi * g, -160.f), 160.f);  // exp is 0 or inf past the ends; g = +-inf shows in f
+    const float n = rintf(a);
+    const float e = ldexpf(__builtin_amdgcn_exp2f(fmaf(g, -kLo, a - n)), static_cast<int>(n));
+    const float c = g < 0.f ? 0x1p-64f : 1.f;
+    return g * __builtin_amdgcn_rcpf(fmaf(e, c, c)) * c * u;
 }
 
 // VEC: eight columns per thread (inter a multiple of eight, 16-byte aligned rows); else one.

@@ -86,6 +86,20 @@ def test_swiglu(rows, inter):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("inter", [256, 255])
+def test_swiglu_of_very_negative_gates(inter):
+    # SiLU keeps its relative precision down to where exp(-gate) passes the fp32 range (88.7), here scaled up
+    # by the other operand
+    gate = torch.linspace(-88.5, -60.0, inter, device="cuda").bfloat16()
+    up = torch.full((inter,), 2.0 ** 100, device="cuda").bfloat16()
+    out = tkv.tkv_swiglu(torch.cat((gate, up))[None])
+    g = gate.double()
+    ref = g / (1 + torch.exp(-g)) * up.double()
+    assert torch.all(ref < 0)
+    _close(out[0], ref, ref.abs())
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [512, 511])
 def test_infinities_and_nan_as_the_tensor_operations_give_them(n):
     # a row each with +inf, -inf and NaN among its values, and one without; both forms of the row kernels
