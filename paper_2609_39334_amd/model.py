@@ -82,7 +82,22 @@ class SyntheticDecoder:
         tokens, positions: [rows] int64 (the new token and its position in the row's path); dst:
         [rows] int32 pool slots of the new tokens (tkv_bm_append); plan: a decode plan over the rows'
         block tables, which already include the new tokens; k_pools[l], v_pools[l]: layer l's pools
-        [num_blocks, hkv, 16, d] bf16."""
+        [num_blocks, hkv, 16, d] bf16.  With a stream (a torch stream or a raw handle) other than the
+        current one the whole step runs there, after the current stream's work so far and before its
+        later work."""
+        current = torch.cuda.current_stream()
+        if stream is None or getattr(stream, "cuda_stream", stream) == current.cuda_stream:
+            return self._step(tokens, positions, dst, plan, k_pools, v_pools, on_layer)
+        other = stream if hasattr(stream, "cuda_stream") else torch.cuda.ExternalStream(stream)
+        other.wait_stream(current)
+        with torch.cuda.stream(other):
+            logits = self._step(tokens, positions, dst, plan, k_pools, v_pools, on_layer)
+        current.wait_stream(other)
+        logits.record_stream(current)
+        return logits
+
+    def _step(self, tokens, positions, dst, plan, k_pools, v_pools, on_layer):
+        """step on the current stream."""
         s = self.shape
         rows = int(tokens.numel())
         ang = positions.float()[:, None] * self.inv_freq[None, :]
@@ -90,9 +105,9 @@ class SyntheticDecoder:
         x, delta = self.embed[tokens], None  # the residual stream, and what is still to be added to it
         for li, w in enumerate(self.layers):
             qkv = torch.mm(tkv_add_rmsnorm(x, delta, w["ln1"], s.eps), w["wqkv"])
-            q = tkv_rope_append(qkv, cos, sin, dst, s.hq, k_pools[li], v_pools[li], stream)
+            q = tkv_rope_append(qkv, cos, sin, dst, s.hq, k_pools[li], v_pools[li])
             o = torch.empty((rows, s.hq, s.d), dtype=torch.bfloat16, device=x.device)
-            plan.decode(q, k_pools[li], v_pools[li], o, None, stream)
+            plan.decode(q, k_pools[li], v_pools[li], o)
             delta = torch.mm(o.view(rows, s.hq * s.d), w["wo"])
             gu = torch.mm(tkv_add_rmsnorm(x, delta, w["ln2"], s.eps), w["wgu"])
             delta = torch.mm(tkv_swiglu(gu), w["wd"])

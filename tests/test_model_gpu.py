@@ -116,3 +116,36 @@ def test_decoder_step_matches_reference(seed, layers, hq, hkv, d):
     for li in range(layers):
         kl = k_pools[li].view(torch.int16).cpu().numpy()
         assert not (kl[dst // bs, :, dst % bs, :].view(np.uint16) == W.BF16_NAN).any()
+
+
+def test_decoder_step_on_another_stream():
+    # the whole step runs on the stream it is given: the current stream's later work sees its logits and pools
+    # (the other stream is kept busy first), and so does a step whose inputs the current stream makes last
+    import paper_2609_39334_amd as tkv
+    from paper_2609_39334_amd.model import DecoderShape, SyntheticDecoder
+    rows, nb, hq, hkv, d = 6, 32, 4, 2, 64
+    model = SyntheticDecoder(DecoderShape(2, 256, hq, hkv, d, 512, 1000), "cuda", 3)
+    tables = np.concatenate([np.r_[0:4, 4 + 2 * r:6 + 2 * r] for r in range(rows)]).astype(np.int32)
+    ptr = np.arange(rows + 1, dtype=np.int32)
+    plan = tkv.Plan((hq, hkv, d, 16, nb), ptr, 6 * ptr, tables, np.full(nb, 16, np.int32))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    pools = [[torch.randn((nb, hkv, 16, d), generator=g, device="cuda").bfloat16() for _ in range(2)] for _ in "kv"]
+    tokens = torch.randint(0, 1000, (rows,), generator=g, device="cuda")
+    positions = torch.full((rows,), 95, device="cuda")
+    dst = torch.tensor([16 * (6 + 2 * r) - 1 for r in range(rows)], dtype=torch.int32, device="cuda")
+    want = model.step(tokens, positions, dst, plan, *pools).clone()
+    busy = torch.zeros(256 << 20, dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    for stream in (side, side.cuda_stream, torch.cuda.current_stream().cuda_stream):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(50):
+                busy.add_(1)
+        late = tokens.clone().zero_()
+        for _ in range(50):
+            busy.view(-1)[:1 << 20].add_(1)
+        late.copy_(tokens)
+        got = model.step(late, positions, dst, plan, *pools, stream).clone()
+        late.zero_()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
