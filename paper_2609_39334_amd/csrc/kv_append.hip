@@ -14,10 +14,12 @@
 namespace {
 
 constexpr int kAppendThreads = 256;
-// Calls that read and write at least this much go past the caches (non-temporal): it is the Infinity
-// Cache's size, so nothing of a larger call would still be there for its reader, and the lines it would
-// displace are kept.  437,617 tokens of 2 x 128 (723 MB): 134.8 us (5.4 TB/s) through the caches, 118.9 us
-// (6.1 TB/s) past them.  Smaller calls stay in the caches for the attention that follows.
+// Calls of new rows that make at least this much of reads and writes together, skipped ones counted (their
+// number is on the device), go past the caches with non-temporal loads and stores: 437,617 tokens of 2 x 128
+// (723 MB) take 134.8 us (5.4 TB/s) through the caches, 118.9 us (6.1 TB/s) past them.  The line is where an
+// attention call that reads the rows next no longer loses by it, append and decode together, through the
+// caches against past them: 28.2 / 33.0 us at 64 MiB, 41.1 / 45.1 at 128, 73.4 / 73.2 at 256, 109.5 / 110.2
+// at 384, 145 / 137 at 512, 225 / 201 at 768.
 constexpr int64_t kStreamBytes = int64_t{256} << 20;
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
