@@ -17,11 +17,11 @@
 //   Lane l of a part starts at F_l = P_i + f_i (part start + lanes before it, by a fixed shuffle
 //   pattern), and its token j is at F_l + f_i (w of its logits up to j, in token order).
 // A draw finds the tile with P_i <= u Z < P_{i+1} and the part whose start is the last at or below
-// u Z; one wave reloads that part and repeats the same arithmetic; the last lane that starts at or
-// below u Z scans its 16 logits, and a target its rounding leaves past its last token goes to its last
-// token with a weight.  Zero weights (logit -inf) are never drawn.  Grouping: each draw that is the
-// first of its token counts the token's draws and writes it at its rank among the distinct tokens, so
-// groups come out in ascending token order.
+// u Z; one wave reloads that part and repeats the same arithmetic; of the lanes that own a weight, the
+// last that starts at or below u Z scans its 16 logits, and a target its rounding leaves past its last
+// token goes to its last token with a weight.  Zero weights (logit -inf, or so low that exp2 gives 0) are
+// never drawn.  Grouping: each draw that is the first of its token counts the token's draws and writes it
+// at its rank among the distinct tokens, so groups come out in ascending token order.
 //
 // What bounds it: reading the logits.  A wave works on its own tile, so nothing waits at a barrier
 // until the row is read, and a workgroup of W waves keeps W tiles (16 KB each) in flight.  The tile
@@ -149,7 +149,7 @@ __device__ __forceinline__ float lane_sum(const float (&x)[kPerLane], float b, f
 
 // W waves per row, NT: non-temporal loads, TILES: the most tiles a row may have.  Four waves are for
 // many short rows, which want as many workgroups on a CU as fit (six: 1,500 rows of 600 tokens 15.1 ->
-// 11.8 us against five).
+// 11.8 us against five; two of its registers go to scratch for that).
 template <int W, bool NT, int TILES>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ? 6 : 4))) void cd_sample(const float* __restrict__ logits, int vocab, float c,
                                                     const float* __restrict__ uniform,
@@ -254,24 +254,29 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ?
     // (once for a run of draws in one part)
     int held = -1;  // the part whose logits and starts are in x and start
     float x[kPerLane], start = 0.f;
+    uint64_t weighted = 0;  // the lanes with a weight in it
     for (int k = w; k < n; k += W) {
         const int i = __builtin_amdgcn_readfirstlane(tile_of[k]);
         if (i >= n_tiles) continue;
         const float tg = target[k], b = base[i], p0 = P[i];
         const float f = __builtin_amdgcn_exp2f((b - mx) * c);
         const float4 ps = part[i];
-        const int pi = __builtin_amdgcn_readfirstlane(p0 + f * ps.z <= tg ? 3 : p0 + f * ps.y <= tg ? 2 : p0 + f * ps.x <= tg ? 1 : 0);
+        // (the sums that P is made of, so the part has a weight: behind one without, the next starts no later)
+        const int pi = __builtin_amdgcn_readfirstlane(fmaf(f, ps.z, p0) <= tg ? 3 : fmaf(f, ps.y, p0) <= tg ? 2 : fmaf(f, ps.x, p0) <= tg ? 1 : 0);
         const int a0 = i * kTile + pi * kPart;
         if (a0 != held) {
             held = a0;
             load16(row, vocab, a0, lane, x);
-            const float incl = wave_scan(lane_sum(x, b, c), lane);
+            const float sum = lane_sum(x, b, c);
+            weighted = __builtin_amdgcn_ballot_w64(sum > 0.f);
+            const float incl = wave_scan(sum, lane);
             float excl = __shfl_up(incl, 1);
             if (lane == 0) excl = 0.f;
             start = p0 + f * ((pi == 0 ? 0.f : pi == 1 ? ps.x : pi == 2 ? ps.y : ps.z) + excl);
         }
-        const uint64_t below = __builtin_amdgcn_ballot_w64(start <= tg);
-        if (lane == 63 - __builtin_clzll(below | 1)) {
+        // (the scan's sums do not rise evenly: lanes behind the last weight may start at or below the target)
+        const uint64_t below = weighted & __builtin_amdgcn_ballot_w64(start <= tg);
+        if (lane == (below ? 63 - __builtin_clzll(below) : __builtin_ctzll(weighted | uint64_t{1} << 63))) {
             const int a = a0 + lane * kPerLane;
             int pick = -1, last = -1;
             float acc = 0.f;
@@ -286,12 +291,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ?
         }
     }
     __syncthreads();
-    // targets that no lane took (u Z rounded up to Z, or the gap before a zero-weight run):
-    // the last token with a weight at or before the target's tile end
+    // targets past every tile (u Z = Z, for u = 1): the row's last token with a weight
     for (int k = t; k < n; k += 64 * W) {
         if (tok[k] >= 0) continue;
-        int j = min(vocab, (min(tile_of[k], n_tiles - 1) + 1) * kTile) - 1;
-        while (j > 0 && row[j] == -INFINITY) --j;
+        int j = vocab - 1;
+        while (j > 0 && __builtin_amdgcn_exp2f((row[j] - mx) * c) == 0.f) --j;
         tok[k] = j;
     }
     __syncthreads();

@@ -119,6 +119,30 @@ def test_cd_sample_workgroup_sizes(n_rows, vocab):
                 tok[sub], cnt[sub], ng[rows])
 
 
+@pytest.mark.parametrize("n_rows", [1, 300, 20000])
+@pytest.mark.parametrize("mask", [-3.4028234663852886e38, float("-inf"), -1e4])
+def test_cd_sample_never_draws_a_zero_weight(n_rows, mask):
+    # Weights 1, 2^-24 and 2^-24 in the second to fourth lane of a part, everything else masked, and a target
+    # of exactly 1 under a total of 1 + 2^-23: lanes behind the weights, whose sums are added in another order,
+    # start at 1 as well.  c = 1 and whole logits, so that every weight is a power of two.  Then u = 1, past
+    # every tile, and draws over the whole range.  (16, 4 and 8 waves a row, the last with non-temporal loads.)
+    import paper_2609_39334_amd as tkv
+    vocab = 3 * 4096 + 5
+    temperature = float(np.float32(1.4426950408889634))
+    logits = torch.full((n_rows, vocab), mask, dtype=torch.float32, device="cuda")
+    first = 4096 + 1024                       # the second part of the second tile
+    at = [first + 16 * 1 + 3, first + 16 * 2, first + 16 * 3 + 15]
+    logits[:, at[0]] = 24.0
+    logits[:, at[1]] = logits[:, at[2]] = 0.0
+    u = torch.tensor([1 - 2.0 ** -23, 1.0, 0.0, 0.5, 1 - 2.0 ** -24], dtype=torch.float32, device="cuda")
+    off = torch.arange(n_rows + 1, dtype=torch.int32, device="cuda") * len(u)
+    tok, cnt, ng = tkv.tkv_cd_sample(logits, temperature, off, u.repeat(n_rows), len(u))
+    tok, cnt, ng = tok.view(n_rows, -1).cpu().numpy(), cnt.view(n_rows, -1).cpu().numpy(), ng.cpu().numpy()
+    for r in range(n_rows):
+        drawn = dict(zip(tok[r, :ng[r]].tolist(), cnt[r, :ng[r]].tolist()))
+        assert set(drawn) <= set(at) and sum(drawn.values()) == len(u) and drawn[at[0]] >= 2 and at[2] in drawn
+
+
 def test_cd_sample_distribution():
     # 100 rows of the same 50-token distribution, 1024 draws each: chi-square against the probabilities
     from scipy.stats import chi2
