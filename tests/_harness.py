@@ -72,7 +72,7 @@ def worker_threads() -> int:
     return max(1, min(16, len(os.sched_getaffinity(0))))
 
 
-def oracle_check(q_bits, k_f32, v_f32, tables, block_len, q_lens, o, lse, rows=None, threads=None):
+def oracle_check(q_bits, k_f32, v_f32, tables, block_len, q_lens, o, lse, rows=None, threads=None, few=0):
     """Compare device results with the oracle, row by row.
 
     The oracle runs on sub-batches of rows in parallel threads (BLAS single-threaded inside each):
@@ -80,7 +80,8 @@ def oracle_check(q_bits, k_f32, v_f32, tables, block_len, q_lens, o, lse, rows=N
     would for those rows.  q_bits: [n_qtok, hq, d] bf16 bits; k_f32 / v_f32: the pools widened to
     float32; o, lse: the device results as float32 arrays.  Returns a dict with the max and mean
     absolute error of o, the max absolute error of lse, the number of tokens compared and whether
-    every compared output is finite."""
+    every compared output is finite.  Tokens that see fewer than `few` keys stay out of "max" and
+    "lse_max" and have their own, "max_few" and "lse_max_few"."""
     from concurrent.futures import ThreadPoolExecutor
     from threadpoolctl import threadpool_limits
     import oracle
@@ -101,12 +102,16 @@ def oracle_check(q_bits, k_f32, v_f32, tables, block_len, q_lens, o, lse, rows=N
         og, lg = o[idx], lse[idx]
         err = np.abs(og - o_ref)
         lerr = np.abs(lg - l_ref)
-        return (float(err.max()), float(err.sum()), int(err.size), float(lerr.max()),
-                bool(np.isfinite(og).all() and np.isfinite(lg).all()), len(idx))
+        n_keys = np.concatenate([np.arange(int(q_lens[r])) + 1 - int(q_lens[r]) +
+                                 sum(int(block_len[b]) for b in tables[r]) for r in sub])
+        low = n_keys < few
+        return (float(err[~low].max(initial=0.0)), float(err.sum()), int(err.size), float(lerr[~low].max(initial=0.0)),
+                bool(np.isfinite(og).all() and np.isfinite(lg).all()), len(idx), float(err[low].max(initial=0.0)),
+                float(lerr[low].max(initial=0.0)))
 
     with threadpool_limits(1):
         with ThreadPoolExecutor(threads) as ex:
             res = list(ex.map(run, [s for s in subs if s]))
     return {"max": max(r[0] for r in res), "mean": sum(r[1] for r in res) / sum(r[2] for r in res),
             "lse_max": max(r[3] for r in res), "finite": all(r[4] for r in res),
-            "tokens": sum(r[5] for r in res)}
+            "tokens": sum(r[5] for r in res), "max_few": max(r[6] for r in res), "lse_max_few": max(r[7] for r in res)}
