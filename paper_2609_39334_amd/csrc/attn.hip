@@ -567,9 +567,14 @@ __device__ __forceinline__ void wave_worker(int w, int lane, const int4* __restr
 // swizzles: the ones below measured zero bank-conflict cycles (SQ_LDS_BANK_CONFLICT) for their own
 // read pattern, whereas one swizzle for both cost 4 cycles per K read (or 2 per V read).  Both depend
 // on r mod 16 only, so a block's rows carry the same pattern wherever the block sits in the stage.
-// (These two are for heads of 128: heads of 64 are always tile_item32's.)
-__device__ __forceinline__ int tile_swz_k(int r) { return r & 15; }
-__device__ __forceinline__ int tile_swz_v(int r) { return (2 * (r & 7)) ^ ((r >> 3) & 1); }
+template <int D>
+__device__ __forceinline__ int tile_swz_k(int r) {
+    return D == 128 ? r & 15 : r & 7;
+}
+template <int D>
+__device__ __forceinline__ int tile_swz_v(int r) {
+    return D == 128 ? (2 * (r & 7)) ^ ((r >> 3) & 1) : r & 7;
+}
 template <int D>
 constexpr int tile_buf_bytes() {
     return 64 * D * 2;
@@ -609,8 +614,8 @@ __device__ __forceinline__ void stage_fetch(const uint16_t* __restrict__ kpool, 
     for (int i = 0; i < 16 / RPI; ++i) {
         const int r = i * RPI + lane / CPR;
         const int row_off = min(r, last) * D * 2;
-        const int koff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_k32<D>(r) : tile_swz_k(r))) * 16);
-        const int voff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_v32<D>(r) : tile_swz_v(r))) * 16);
+        const int koff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_k32<D>(r) : tile_swz_k<D>(r))) * 16);
+        const int voff = row_off + (((lane % CPR) ^ (W32 ? tile_swz_v32<D>(r) : tile_swz_v<D>(r))) * 16);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void_ptr)(kdst + i * 1024), 16, koff, 0, 0, 0);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void_ptr)(vdst + i * 1024), 16, voff, 0, 0, 0);
     }
@@ -625,21 +630,19 @@ __device__ __forceinline__ void stage_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// One workgroup of four waves per tile item: a tile of up to 128 query rows (wave w owns rows
-// 32w .. 32w+31 as two column tiles of 16) against the item's key blocks, four blocks per stage.
-// Stage s+1 is fetched into the other pair of LDS buffers while stage s is contracted; one barrier per
-// stage (a buffer is rewritten only after every wave has passed the barrier that follows its last use).
-// The stage loop is unrolled by two so that each stage names its buffers statically: the compiler then knows
-// that the reads of one buffer do not depend on the fetch into the other.
-template <int D>
+// One workgroup of four waves (T = 2) or eight (T = 1) per tile item: a tile of up to 128 query rows (wave w
+// owns rows 16Tw .. 16Tw+16T-1 as T column tiles of 16) against the item's key blocks, four blocks per stage
+// (fetched by waves 0-3).  Stage s+1 is fetched into the other pair of LDS buffers while stage s is contracted;
+// one barrier per stage (a buffer is rewritten only after every wave has passed the barrier that follows its
+// last use).  The stage loop is unrolled by two so that each stage names its buffers statically: the compiler
+// then knows that the reads of one buffer do not depend on the fetch into the other.
+template <int D, int T>
 __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::TokDesc* __restrict__ toks,
                                           const tkv::BlkDesc* __restrict__ blks, const uint16_t* __restrict__ q,
                                           const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool,
                                           uint16_t* __restrict__ o, float* __restrict__ lse, uint16_t* __restrict__ po,
                                           float* __restrict__ plse, int hq, int hkv, int G, float sl2, uint8_t* k0,
                                           uint8_t* v0, uint8_t* k1, uint8_t* v1) {
-    static_assert(D == 128, "the swizzles");
-    constexpr int T = 2;
     constexpr int RB = 2 * D;  // bytes per K/V row in the stage buffers
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -673,15 +676,15 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
     // chunk 4kk + kg, i.e. koff ^ 64kk.  V, transposed reads: lane (col, kg) reads row
     // 4kg + col/4, bytes 8(col & 3) .. +7 of the 32-byte column run of output tile ct, i.e.
     // voff ^ 32ct.  (The XORs touch only the chunk-index bits of the offsets.)
-    const int koff = col * RB + 16 * (kg ^ tile_swz_k(col));
+    const int koff = col * RB + 16 * (kg ^ tile_swz_k<D>(col));
     const int vrow = 4 * kg + (col >> 2);
-    const int voff = vrow * RB + 16 * (((col & 3) >> 1) ^ tile_swz_v(vrow)) + 8 * (col & 1);
+    const int voff = vrow * RB + 16 * (((col & 3) >> 1) ^ tile_swz_v<D>(vrow)) + 8 * (col & 1);
 
     // block descriptors of a stage: lane l holds block 4s + (l & 3) (the item's last block past its end)
     auto stage_desc = [&](int st) { return bd[min(4 * st + (lane & 3), nb - 1)]; };
     int2 dcur = stage_desc(0), dnxt = stage_desc(1);
     const int wblk = wave * 16 * RB;  // this wave's block within a stage buffer
-    {
+    if (T == 2 || wave < 4) {
         const int len = wave < nb ? __builtin_amdgcn_readlane(dcur.y, wave) : 0;
         stage_fetch<D, false>(kpool, vpool, static_cast<size_t>(__builtin_amdgcn_readlane(dcur.x, wave)) * blk_stride + kvh_off,
                        len, lane, k0 + wblk, v0 + wblk);
@@ -692,7 +695,7 @@ __device__ __forceinline__ void tile_item(const tkv::ItemDesc& it, const tkv::To
     auto stage = [&](int st, const uint8_t* ks, const uint8_t* vs, uint8_t* kn, uint8_t* vn) {
         stage_barrier();
         // fetch the next stage while this one is contracted
-        if (st + 1 < n_stages) {
+        if (st + 1 < n_stages && (T == 2 || wave < 4)) {
             const int bn = 4 * (st + 1) + wave;
             const int len = bn < nb ? __builtin_amdgcn_readlane(dnxt.y, wave) : 0;
             stage_fetch<D, false>(kpool, vpool,
@@ -1131,7 +1134,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             tile_item32<D, 1, 4>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0,
                                  lds_k1, lds_v1, nullptr);
         else
-            tile_item<D>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1,
+            tile_item<D, 2>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1,
                          lds_v1);
         return;
     }
@@ -1144,15 +1147,33 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 }
 
 // Few tile items and no wave-grid work (a small verification batch): the chip has a CU for every
-// tile, and a tile's walk over its keys sets the call's time.  Eight waves share a tile: R waves of 32
-// rows, times 8 / R groups of waves that each take a part of every stage's keys with a softmax of their
-// own and join at the end, so the walk is half as many stages as four waves make of it.  R = 4 (128 rows,
-// two groups of 64 keys a stage): every stage buffer is read by four waves of 32 rows, where eight waves
-// of 16 rows read each of them eight times.  R = 2 (64 rows, four groups of 32 keys a stage): half the
-// work for a CU, where the chip has CUs for twice the tiles.  Bound by a stage's chain (LDS reads ->
-// scores -> maxima -> exponentials -> PV) with two waves per SIMD.  512 tokens of 28/4/128 heads under
-// 1,024 keys and more: 29.6 us as eight waves of 16 rows, 28.6 us with R = 4 (116 tiles), 23.8 us with
-// R = 2 (228 tiles).
+// tile, and a tile's walk over its keys sets the call's time.  Eight waves share a tile, in one of three
+// forms (tile8_form in plan.cpp has the line between them).
+//
+// Eight waves of 16 rows, for short walks.
+template <int D>
+__global__ __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_tile8_rows16(
+    const tkv::ItemDesc* __restrict__ items, int n_tile, const tkv::TokDesc* __restrict__ toks,
+    const tkv::BlkDesc* __restrict__ blks, const uint16_t* __restrict__ q, const uint16_t* __restrict__ kpool,
+    const uint16_t* __restrict__ vpool, uint16_t* __restrict__ o, float* __restrict__ lse, uint16_t* __restrict__ po,
+    float* __restrict__ plse, int hq, int hkv, int G, float sl2) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_k0[tile_buf_bytes<D>()];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_v0[tile_buf_bytes<D>()];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_k1[tile_buf_bytes<D>()];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_v1[tile_buf_bytes<D>()];
+    const int b = blockIdx.x;
+    if (b >= n_tile) return;
+    const tkv::ItemDesc it = items[b];
+    tile_item<D, 1>(it, toks, blks, q, kpool, vpool, o, lse, po, plse, hq, hkv, G, sl2, lds_k0, lds_v0, lds_k1, lds_v1);
+}
+
+// R waves of 32 rows, times 8 / R groups of waves that each take a part of every stage's keys with a softmax
+// of their own and join at the end, so the walk is half as many stages as four waves make of it.  R = 4 (128
+// rows, two groups of 64 keys a stage): every stage buffer is read by four waves of 32 rows, where eight waves
+// of 16 rows read each of them eight times.  R = 2 (64 rows, four groups of 32 keys a stage): half the work
+// for a CU, where the chip has CUs for twice the tiles.  Bound by a stage's chain (LDS reads -> scores ->
+// maxima -> exponentials -> PV) with two waves per SIMD.  512 tokens of 28/4/128 heads under 1,024 keys and
+// more: 29.6 us as eight waves of 16 rows, 28.6 us with R = 4 (116 tiles), 23.8 us with R = 2 (232 tiles).
 template <int D, int R>
 __global__ __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_tile8(
     const tkv::ItemDesc* __restrict__ items, int n_tile, const tkv::TokDesc* __restrict__ toks,
@@ -1468,18 +1489,20 @@ static int launch_d(const tkv_plan* p, uint8_t* ws, const void* q, const void* k
     const int grid = runs > 0 ? 2 * R * runs + std::max(0, (n_tile + R - 1) / R * R - R * runs) +
                                     std::max(0, (n_wave_wg + 7) / 8 * 8 - R * runs)
                               : (n_tile + 7) / 8 * 8 + (n_wave_wg + 7) / 8 * 8;
-    if (p->tile8 && n_wave_wg == 0 && n_tile > 0)
-        hipExtLaunchKernelGGL((p->tile_rows == kTileRowsSmall ? attn_tile8<D, 2> : attn_tile8<D, 4>), dim3(static_cast<unsigned>(n_tile)), dim3(2 * kThreads), 0, st,
-                              ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, 0, items, n_tile, toks, blks,
-                              static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
-                              static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,
-                              p->group, sl2);
-    else if (grid > 0)
+    if (p->tile8 != kTile8None && n_wave_wg == 0 && n_tile > 0) {
+        const auto kernel = p->tile8 == kTile8Rows16 ? attn_tile8_rows16<D> : p->tile8 == kTile8Groups4 ? attn_tile8<D, 2>
+                                                                                                  : attn_tile8<D, 4>;
+        hipExtLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_tile)), dim3(2 * kThreads), 0, st, ev ? ev[0] : nullptr,
+                              ev ? ev[1] : nullptr, 0, items, n_tile, toks, blks, static_cast<const uint16_t*>(q),
+                              static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o),
+                              lse, po, plse, hq, hkv, p->group, sl2);
+    } else if (grid > 0) {
         hipExtLaunchKernelGGL((D == 64 || p->tile32 ? attn_fwd<D, true> : attn_fwd<D, D == 64>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, st,
                               ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, 0, items, n_tile, n_wave_wg, runs, toks, blks,
                               wdesc, woff, wtiles, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                               static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, po, plse, hq, hkv,
                               p->group, sl2);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(TKV_EHIP, "attention launch: %s", hipGetErrorString(e));
     if (!p->merges.empty()) {

@@ -36,6 +36,10 @@ constexpr int kWaveWorkers = 2048;  // waves of the wave kernel: 2 workgroups of
 constexpr int kWaveWG = 4;      // waves per workgroup of the wave kernel (independent; no barriers)
 constexpr int kTile8MaxItems = 256;  // tile items (and no wave grid) up to which 8-wave workgroups run them: one per CU
 constexpr int kTileRowsSmall = 64;   // rows of a tile of a batch so small that the chip has a CU for every such tile
+// How 8-wave workgroups share a tile: waves of 16 rows each; four waves of 32 rows times two groups of keys;
+// or (tiles of at most kTileRowsSmall rows) two waves of 32 rows times four groups
+enum Tile8 : int32_t { kTile8None, kTile8Rows16, kTile8Groups2, kTile8Groups4 };
+constexpr int kTile8ShortStages = 5;  // average stages (of four blocks) of an item up to which they are waves of 16 rows
 constexpr int kInterleaveRun = 32;   // workgroups per run when tile items and wave-grid workgroups alternate:
                                      // 8 XCDs x 4 shader engines, one workgroup of a kind per engine
 constexpr int32_t kNoLimit = 1 << 30;  // causal limit of a q_len-1 token: it sees its whole path (kv_len <= 2^30)
@@ -135,9 +139,9 @@ struct tkv_plan {
     std::vector<int32_t> wave_off;            // [n_waves + 1] wave w's further items: [off[w], off[w+1])
     std::vector<int32_t> wave_tiles;          // [n_waves] column tiles of the wave's items (0: no work)
     int32_t n_slots = 0;
-    int32_t tile_rows = 0;  // query rows of a tile item: kTileRowsWG, or kTileRowsSmall (tile8 plans only)
+    int32_t tile_rows = 0;  // most query rows of a tile item: kTileRowsWG, or kTileRowsSmall (tile8 plans only)
     bool tile32 = false;  // attn_fwd contracts its tile items with 32x32x16 MFMAs, not 16x16x32
-    bool tile8 = false;  // tile items only, few enough to run as 8-wave workgroups (kTile8MaxItems)
+    tkv::Tile8 tile8 = tkv::kTile8None;  // set: tile items only, few enough to run as 8-wave workgroups (kTile8MaxItems)
     // workspace layout (byte offsets)
     size_t off_items = 0, off_toks = 0, off_blks = 0, off_merges = 0, off_mslots = 0, off_wdesc = 0, off_woff = 0, off_wtiles = 0;
     size_t off_po = 0, off_plse = 0, desc_bytes = 0, total_bytes = 0;

@@ -281,6 +281,23 @@ __attribute__((noinline)) int32_t shared_chunk_blocks(const tkv_shape& s, int32_
     return static_cast<int32_t>(len);
 }
 
+// How eight waves share each of a plan's tiles.  The groups of keys that halve or quarter a walk join through
+// LDS at its end, which takes as long as two or three stages: where an item walks up to five stages on average,
+// waves of 16 rows are as fast or faster (28/4 heads of 128, 68 items of one stage 7.2 against 7.9 us; 64/1,
+// 108 items of two to three 7.5 against 9.4 us; heads of 64 0-5%), from six on they lose (6-30% at 12-30).
+// Four groups where the tiles leave two waves' rows at most (15/5 heads, tiles of 48 rows, 16 stages:
+// 26.1 against 28.4 us with two).
+__attribute__((noinline)) tkv::Tile8 tile8_form(const std::vector<ItemDesc>& items, int32_t G) {
+    int64_t stages = 0;
+    int32_t most = 0;
+    for (const ItemDesc& it : items) {
+        stages += (it.n_blk + 3) >> 2;
+        most = std::max(most, it.n_tok);
+    }
+    if (stages <= tkv::kTile8ShortStages * static_cast<int64_t>(items.size())) return tkv::kTile8Rows16;
+    return most * G <= tkv::kTileRowsSmall ? tkv::kTile8Groups4 : tkv::kTile8Groups2;
+}
+
 // Whether attn_fwd contracts the tile items with 32x32x16 MFMAs.  They take half the issue slots of 16x16x32
 // but move the accumulators twice as often per flop, and are the faster ones until long walks keep the whole
 // chip busy and the clock falls.  So the line is on the stages (64 keys) that an item walks on average, by
@@ -348,7 +365,7 @@ void clear_plan(tkv_plan* p) {
     p->n_slots = 0;
     p->tile_rows = 0;
     p->tile32 = false;
-    p->tile8 = false;
+    p->tile8 = tkv::kTile8None;
     p->off_items = p->off_toks = p->off_blks = p->off_merges = p->off_mslots = p->off_wdesc = p->off_woff = p->off_wtiles = 0;
     p->off_po = p->off_plse = p->desc_bytes = p->total_bytes = 0;
     tkv::give_image(std::move(p->image), p->image_cap);
@@ -503,7 +520,7 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         st.n_qtok = n_rows ? q_indptr[n_rows] : 0;
         // A batch of verify rows only, so small that the chip has a CU for every tile of kTileRowsSmall
         // rows, takes tiles of that size; every other plan's tiles have kTileRowsWG rows.  (512 tokens of
-        // 28/4 heads, 228 tiles of 64 rows or 116 of 128: 23.8 against 28.6 us.  Past one tile per CU the
+        // 28/4 heads, 232 tiles of 64 rows or 116 of 128: 23.8 against 28.6 us.  Past one tile per CU the
         // smaller tiles would only read the keys twice as often.)
         const int64_t tile8_max = opt(&tkv_plan_options::tile8_max_items, tkv::kTile8MaxItems);
         p->tile_rows = tkv::kTileRowsSmall;
@@ -1041,7 +1058,8 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         st.n_idle_waves = static_cast<int32_t>(std::count(p->wave_tiles.begin(), p->wave_tiles.end(), 0));
         // a plan of a few tile items and nothing else gives each tile a CU to itself: eight waves then
         // share the tile's rows and keys, which shortens its walk
-        p->tile8 = p->wave_items.empty() && !p->items.empty() && static_cast<int64_t>(p->items.size()) <= tile8_max;
+        p->tile8 = p->wave_items.empty() && !p->items.empty() && static_cast<int64_t>(p->items.size()) <= tile8_max
+                       ? tile8_form(p->items, G) : tkv::kTile8None;
         p->tile32 = takes_mfma32(s.d, p->items);
         st.n_slots = p->n_slots;
         st.n_merge = static_cast<int32_t>(p->merges.size());

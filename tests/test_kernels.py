@@ -327,10 +327,9 @@ def _check_with_few_keys(b, o, lse, k, v, q):
 @pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 4, 64)])
 @pytest.mark.parametrize("tokens", [300, 750, 2000, 5200])
 def test_verify_tile_variants_at_their_edges(hq, hkv, d, tokens):
-    # rows of 1 to 20 blocks (key groups without a key, partial stages and blocks), whole and partial
-    # tiles, in batches of each tile variant: 64-row tiles with four key groups, 128-row tiles with two,
-    # and the 4-wave kernel (up to and past 1,024 tile items; test_verify_tiles_by_walk_length has both its
-    # matrix instructions)
+    # rows of 1 to 20 blocks (partial stages and blocks), whole and partial tiles, in batches of 64-row
+    # tiles and of 128-row tiles, on the 8-wave and on the 4-wave kernel (up to and past 1,024 tile items;
+    # the two tests below have their forms by the length of the walks)
     g = hq // hkv
     wl = W.Workload(f"tile_edges_{tokens}", W.Shape(hq, hkv, d), 50, note="verify-only batch")
     rt = np.random.default_rng([50, tokens])
@@ -382,3 +381,37 @@ def test_verify_tiles_by_walk_length(hq, hkv, d, n_items, ctx, wide):
     stages = sum(t * -(-len(table) // 4) for t, table in zip(tiles, b.tables))
     assert st["n_items_wave"] == 0 and st["n_items"] == sum(tiles)
     assert (sum(tiles) <= 384 or stages <= 24 * sum(tiles)) == wide
+
+
+@pytest.mark.parametrize("hq,hkv,d,ctx,rows,q_len,form", [
+    # items of up to five stages of four blocks on average: waves of 16 rows.  Tiles of 64 and 128 rows
+    (28, 4, 128, 200, 9, (10, 60), "rows16"), (16, 4, 64, 250, 9, (16, 60), "rows16"), (8, 2, 64, 40, 24, (33, 257), "rows16"),
+    (64, 1, 128, 100, 6, (1, 1), "rows16"), (15, 5, 128, 250, 5, (12, 20), "rows16"),
+    # longer walks: two groups of keys on tiles of 128 rows, four on tiles of at most 64
+    (28, 4, 128, 500, 10, (64, 130), "groups2"), (8, 2, 64, 600, 20, (64, 257), "groups2"), (40, 2, 128, 16500, 12, (1, 1), "groups2"),
+    (28, 4, 128, 400, 9, (10, 60), "groups4"), (16, 4, 64, 350, 9, (16, 60), "groups4"), (15, 5, 128, 3000, 1, (16, 16), "groups4"),
+    (64, 1, 128, 370, 5, (1, 1), "groups4"),
+])
+def test_small_tile_plans_by_walk_length(hq, hkv, d, ctx, rows, q_len, form):
+    # the three forms of 8-wave tiles; every fifth row has no context (key groups without a key)
+    g = hq // hkv
+    wl = W.Workload(f"tile8_{ctx}_{rows}", W.Shape(hq, hkv, d), 52, note="a plan of tile items alone")
+    rt = np.random.default_rng([52, ctx, rows])
+    root = wl.extend(-1, rt.integers(0, 32000, ctx), True)
+    cands = []
+    for r in range(rows):
+        n = int(rt.integers(q_len[0], q_len[1] + 1))
+        base = -1 if r % 5 == 4 and n * g >= 64 else root
+        cands.append((wl.extend(base, rt.integers(0, 32000, n), True), n))
+    wl.prune(root)
+    wl.launch("verify", cands)
+    wl.finalize()
+    b, o, lse, k, v, q, st, same = run_gpu(wl, 0, repeat=2)
+    _check_with_few_keys(b, o, lse, k, v, q)
+    import paper_2609_39334_amd as tkv
+    qi, ki, kb = b.arrays()
+    items = tkv.Plan((hq, hkv, d, 16, wl.num_blocks), qi, ki, kb, b.block_len, b.mult, upload=False).view()["items"]
+    stages, most = sum(-(-int(it[4]) // 4) for it in items), max(int(it[2]) for it in items) * g
+    _log(f"    {len(items)} items of {stages / len(items):.1f} stages, {most} rows")
+    assert same and st["n_items_wave"] == 0 and len(items) <= 256
+    assert form == ("rows16" if stages <= 5 * len(items) else "groups4" if most <= 64 else "groups2")
