@@ -301,20 +301,21 @@ __attribute__((noinline)) tkv::Tile8 tile8_form(const std::vector<ItemDesc>& ite
 // Whether attn_fwd contracts the tile items with 32x32x16 MFMAs.  They take half the issue slots of 16x16x32
 // but move the accumulators twice as often per flop, and are the faster ones until long walks keep the whole
 // chip busy and the clock falls.  So the line is on the stages (64 keys) that an item walks on average, by
-// the number of items.  Time with 16x16x32 over that with 32x32x16, verify batches of 28/4, 32/8 and 12/2
-// heads of 128:
+// the number of items and by how many of an item's four waves have rows.  Time with 16x16x32 over that with
+// 32x32x16, verify batches of 28/4, 32/8 and 12/2 heads of 128, tiles mostly full:
 //   items         4 stages   8          11         14-18       20-24       28-38       67 and more
 //   to 384        1.16       1.08-1.09  1.06       1.02-1.05   1.02-1.04   1.00-1.03   1.01-1.02
 //   to 768        1.09-1.20  1.06-1.10  1.02-1.11  1.00-1.07   0.98-1.03   0.98-1.02   0.94-1.00
 //   1,000-2,224   1.09-1.12  1.05-1.06  1.00-1.06  0.99-1.01   0.98-1.00   0.96-0.99   0.93-0.98
 //   4,400-8,048   1.11-1.13  1.01-1.03  1.00       0.95-0.99   0.94-0.98   0.96-0.98   0.94-0.95
+// three waves of four: 1.00-1.12 up to 704 items, 0.99-1.11 up to 32 stages, 0.98-1.00 beyond; two to two and
+// a half (450-4,000 items of 5-251 stages): 1.00-1.11.
 // Heads of 64 halve the accumulators: 1.00-1.07 at every size measured (480 to 16,000 items, 11 to 510 stages).
-__attribute__((noinline)) bool takes_mfma32(int32_t d, const std::vector<ItemDesc>& items) {
-    const int64_t n = static_cast<int64_t>(items.size());
-    if (d == 64 || n <= 384) return true;
-    int64_t stages = 0;
-    for (const ItemDesc& it : items) stages += (it.n_blk + 3) >> 2;
-    return stages <= n * (n <= 768 ? 24 : n <= 2048 ? 16 : 8);
+// n: items; blocks: their key blocks (four to a stage); waves: blocks x waves with rows.
+bool takes_mfma32(int32_t d, int64_t n, int64_t blocks, int64_t waves) {
+    if (d == 64 || n <= 384 || 10 * waves <= 27 * blocks) return true;
+    if (10 * waves <= 32 * blocks) return n <= 768 || blocks <= 4 * 32 * n;
+    return blocks <= 4 * n * (n <= 768 ? 24 : n <= 2048 ? 16 : 8);
 }
 
 // The planner's working arrays, kept per thread from one plan to the next (a loop that plans every
@@ -1060,7 +1061,6 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
         // share the tile's rows and keys, which shortens its walk
         p->tile8 = p->wave_items.empty() && !p->items.empty() && static_cast<int64_t>(p->items.size()) <= tile8_max
                        ? tile8_form(p->items, G) : tkv::kTile8None;
-        p->tile32 = takes_mfma32(s.d, p->items);
         st.n_slots = p->n_slots;
         st.n_merge = static_cast<int32_t>(p->merges.size());
 
@@ -1078,6 +1078,7 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
             gid.reset(p->items.size());
             std::vector<std::vector<int32_t>> groups;
             std::vector<int64_t> gcost;
+            int64_t blocks = 0, waves = 0;  // key blocks, and their waves with rows
             // items come in runs of one tile per KV head: the previous item of the same KV head is
             // usually in the same group, found without a lookup
             std::vector<uint64_t> last_key(s.hkv, ~uint64_t{0});
@@ -1097,8 +1098,12 @@ TKV_EXPORT int tkv_plan_create_ex(const tkv_shape* shape, int32_t n_rows, const 
                     last_group[it.kvh] = g2;
                 }
                 groups[g2].push_back(i);
-                gcost[g2] += cost(it);
+                const int64_t c = cost(it);
+                gcost[g2] += c;
+                blocks += it.n_blk;
+                waves += c - 1;
             }
+            p->tile32 = takes_mfma32(s.d, static_cast<int64_t>(p->items.size()), blocks, waves);
             std::vector<int32_t> gorder(groups.size());
             std::iota(gorder.begin(), gorder.end(), 0);
             std::stable_sort(gorder.begin(), gorder.end(), [&](int32_t a2, int32_t b2) { return gcost[a2] > gcost[b2]; });

@@ -355,15 +355,18 @@ def test_verify_tile_variants_at_their_edges(hq, hkv, d, tokens):
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (15, 5, 128), (16, 4, 64)])
-@pytest.mark.parametrize("n_items,ctx,wide", [(350, (1800, 2100), True), (400, (900, 1200), True), (400, (1800, 2100), False)])
-def test_verify_tiles_by_walk_length(hq, hkv, d, n_items, ctx, wide):
+@pytest.mark.parametrize("n_items,ctx,short,wide", [(350, (1800, 2100), False, True), (400, (900, 1200), False, True),
+                                                    (400, (1800, 2100), False, False), (400, (1800, 2100), True, True)])
+def test_verify_tiles_by_walk_length(hq, hkv, d, n_items, ctx, short, wide):
     # 4-wave tile items on either side of the matrix instructions' line: 32x32x16 for heads of 128 up to 384
-    # items or where the walks are short (24 stages of four blocks on average), always for heads of 64.  Every
-    # ninth row has no context.
+    # items, where the walks are short (24 stages of four blocks on average) or a tile's rows few, always for
+    # heads of 64.  Every ninth row has no context.
     g = hq // hkv
     wl = W.Workload(f"tile_walks_{n_items}", W.Shape(hq, hkv, d), 51, note="verify-only batch")
     rt = np.random.default_rng([51, n_items])
-    lengths = [n for n in (10, 17, 33, 64, 65, 100, 130, 257) if n * g >= 64]
+    # (short rows: 64 to 96 query rows)
+    lengths = [n for n in ((10, 13, 16, 21, 24, 31) if short else (10, 17, 33, 64, 65, 100, 130, 257)) if n * g >= 64]
+    lengths = [n for n in lengths if n * g <= 96] if short else lengths
     roots = [wl.extend(-1, rt.integers(0, 32000, int(n)), True) for n in np.linspace(*ctx, 4)]
     cands, tiles = [], []
     while sum(tiles) < n_items:
@@ -378,9 +381,12 @@ def test_verify_tiles_by_walk_length(hq, hkv, d, n_items, ctx, wide):
     b, o, lse, k, v, q, st, same = run_gpu(wl, 0, repeat=2, options={"tile8_max_items": 0})
     _check_with_few_keys(b, o, lse, k, v, q)
     assert same
-    stages = sum(t * -(-len(table) // 4) for t, table in zip(tiles, b.tables))
+    walks = [len(table) for table in b.tables]
+    blocks = sum(t * w for t, w in zip(tiles, walks))
+    waves = sum(w * hkv * sum(-(-min(128 // g, n - a) * g // 32) for a in range(0, n, 128 // g))
+                for w, n in zip(walks, b.q_lens))
     assert st["n_items_wave"] == 0 and st["n_items"] == sum(tiles)
-    assert (sum(tiles) <= 384 or stages <= 24 * sum(tiles)) == wide
+    assert (sum(tiles) <= 384 or blocks <= 4 * 24 * sum(tiles) or 10 * waves <= 32 * blocks) == wide
 
 
 @pytest.mark.parametrize("hq,hkv,d,ctx,rows,q_len,form", [
