@@ -6,11 +6,12 @@
 // One workgroup per row, so rows of every potential size run in one launch.  A draw is the inverse
 // CDF at the caller's uniform u: the first token (in token order) whose cumulative weight exceeds
 // u * Z.  The row is read once, in tiles of 4,096 logits, one wave per tile: lane l owns the 16
-// contiguous logits [16l, 16l + 16) of each of the tile's four 1,024-logit parts.  The kernel's CDF
-// is defined by its own fp32 sums:
+// contiguous logits [16l, 16l + 16) of each of the tile's four 1,024-logit parts.  (Rows of up to 16,384
+// logits take tiles of one part, so that more waves share them.)  The kernel's CDF is defined by its own
+// fp32 sums:
 //   tile i: base b_i = the tile's maximum, w_j = exp2((l_j - b_i) * log2(e) / T);
 //   s_l = w over lane l's 16 logits of a part, added in token order; the part's total is the sum of s_l
-//   over the lanes as a balanced binary tree; the four part totals added in order give the tile total
+//   over the lanes as a balanced binary tree; the part totals added in order give the tile total
 //   T_i and each part's start;
 //   with M the row maximum and f_i = exp2((b_i - M) * log2(e) / T), the tile prefixes
 //   P_0 = 0, P_{i+1} = P_i + f_i T_i, one tile at a time, and Z = P_{n_tiles}.
@@ -39,11 +40,8 @@
 namespace {
 
 constexpr int kPerLane = 16;                  // contiguous logits per lane and part
-constexpr int kParts = 4;                     // parts of a tile
 constexpr int kPart = 64 * kPerLane;          // 1,024 logits
-constexpr int kTile = kParts * kPart;         // 4,096 logits
-constexpr int kMaxTiles = 512;                // vocabulary up to 2,097,152
-constexpr int kShortTiles = 16;               // rows of at most this many tiles take 4 waves when there are many
+constexpr int kMaxVocab = 512 * 4 * kPart;    // 2,097,152
 constexpr int kMaxPotential = 1024;           // draws of one row (grouped in LDS)
 
 typedef float f32x4_t __attribute__((ext_vector_type(4), aligned(4)));  // rows need not start 16-byte aligned
@@ -60,18 +58,18 @@ __device__ __forceinline__ void lanes_agree() {
 // 1-KB runs (lane l takes the l-th 16 bytes of a run) and passed through the wave's 4 KB of LDS, a
 // part at a time; chunk q of a part sits at q ^ ((q / 16) % 4), so that neither the writes (64
 // consecutive chunks) nor the reads (chunks 4l + e) meet in a bank.  NT: non-temporal loads.
-template <bool NT>
+template <int PARTS, bool NT>
 __device__ __forceinline__ void load_tile(const float* __restrict__ tile, int lane, float4* __restrict__ lds,
-                                          float (&x)[kParts][kPerLane]) {
+                                          float (&x)[PARTS][kPerLane]) {
     const f32x4_t* r4 = reinterpret_cast<const f32x4_t*>(tile) + lane;
-    f32x4_t g[kParts][4];
+    f32x4_t g[PARTS][4];
 #pragma unroll
-    for (int p = 0; p < kParts; ++p)
+    for (int p = 0; p < PARTS; ++p)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             g[p][j] = NT ? __builtin_nontemporal_load(r4 + (p * kPart / 4 + 64 * j)) : r4[p * kPart / 4 + 64 * j];
 #pragma unroll
-    for (int p = 0; p < kParts; ++p) {
+    for (int p = 0; p < PARTS; ++p) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int q = 64 * j + lane;
@@ -147,22 +145,22 @@ __device__ __forceinline__ float lane_sum(const float (&x)[kPerLane], float b, f
     return s;
 }
 
-// W waves per row, NT: non-temporal loads, TILES: the most tiles a row may have.  Four waves are for
-// many short rows, which want as many workgroups on a CU as fit (six: 1,500 rows of 600 tokens 15.1 ->
-// 11.8 us against five; two of its registers go to scratch for that).
-template <int W, bool NT, int TILES>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ? 6 : 4))) void cd_sample(const float* __restrict__ logits, int vocab, float c,
-                                                    const float* __restrict__ uniform,
-                                                    const int32_t* __restrict__ draw_off, int32_t n_draws,
-                                                    int32_t* __restrict__ out_tok, int32_t* __restrict__ out_cnt,
-                                                    int32_t* __restrict__ n_groups) {
+// W waves per row, PARTS per tile, NT: non-temporal loads, TILES: the most tiles a row may have.  Four waves
+// are for many rows, which want as many workgroups on a CU as fit: six with four parts (two registers go to
+// scratch for that), eight with one.
+template <int W, int PARTS, bool NT, int TILES>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(PARTS == 1 ? 8 : W == 4 ? 6 : 4))) void cd_sample(
+    const float* __restrict__ logits, int vocab, float c, const float* __restrict__ uniform,
+    const int32_t* __restrict__ draw_off, int32_t n_draws, int32_t* __restrict__ out_tok, int32_t* __restrict__ out_cnt,
+    int32_t* __restrict__ n_groups) {
+    constexpr int kTile = PARTS * kPart;
     __shared__ float base[TILES];             // b_i
-    __shared__ float4 part[TILES];            // the starts of parts 1-3 and the total of tile i
+    __shared__ float part[TILES][PARTS];      // the starts of tile i's parts past the first, and its total
     __shared__ float P[TILES + 1];            // tile prefixes
     __shared__ float row_max;
     __shared__ int32_t wcnt[W];
     // each wave's 4 KB for load_tile; once the row is read, the draws
-    __shared__ float4 shared_mem[W * kPart / 4];
+    __shared__ float4 shared_mem[(W < 4 ? 4 : W) * kPart / 4];
     static_assert(sizeof(shared_mem) >= 16 * kMaxPotential, "room for the draws");
     float* target = reinterpret_cast<float*>(shared_mem);
     int32_t* tok = reinterpret_cast<int32_t*>(shared_mem) + kMaxPotential;
@@ -184,25 +182,28 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ?
 
     // one pass over the row: per tile its maximum, its parts' starts and its total over that base
     for (int i = w; i < n_tiles; i += W) {
-        float x[kParts][kPerLane];
+        float x[PARTS][kPerLane];
         if ((i + 1) * kTile <= vocab) {
-            load_tile<NT>(row + i * kTile, lane, shared_mem + w * (kPart / 4), x);
+            load_tile<PARTS, NT>(row + i * kTile, lane, shared_mem + w * (kPart / 4), x);
         } else {
 #pragma unroll
-            for (int p = 0; p < kParts; ++p) load16(row, vocab, i * kTile + p * kPart, lane, x[p]);
+            for (int p = 0; p < PARTS; ++p) load16(row, vocab, i * kTile + p * kPart, lane, x[p]);
         }
         float m = x[0][0];
 #pragma unroll
-        for (int p = 0; p < kParts; ++p)
+        for (int p = 0; p < PARTS; ++p)
 #pragma unroll
             for (int k = 0; k < kPerLane; ++k) m = fmaxf(m, x[p][k]);
         const float b = wave_tree(m, max2);
-        float s[kParts];
+        float s[PARTS];
 #pragma unroll
-        for (int p = 0; p < kParts; ++p) s[p] = wave_tree(b == -INFINITY ? 0.f : lane_sum(x[p], b, c), add);
+        for (int p = 0; p < PARTS; ++p) s[p] = wave_tree(b == -INFINITY ? 0.f : lane_sum(x[p], b, c), add);
         if (lane == 0) {
             base[i] = b;
-            part[i] = make_float4(s[0], s[0] + s[1], (s[0] + s[1]) + s[2], ((s[0] + s[1]) + s[2]) + s[3]);
+            float sum = s[0];
+            part[i][0] = sum;
+#pragma unroll
+            for (int p = 1; p < PARTS; ++p) part[i][p] = sum += s[p];
         }
     }
     __syncthreads();
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ?
         for (int i0 = 0; i0 < n_tiles; i0 += 64) {
             const int i = i0 + lane;
             const float f = i < n_tiles && base[i] != -INFINITY ? __builtin_amdgcn_exp2f((base[i] - mx) * c) : 0.f;
-            const float total = i < n_tiles ? part[i].w : 0.f;
+            const float total = i < n_tiles ? part[i][PARTS - 1] : 0.f;
             float mine = 0.f;  // P of this lane's tile
             for (int k = 0; k < min(64, n_tiles - i0); ++k) {
                 if (lane == k) mine = sum;
@@ -260,9 +261,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ?
         if (i >= n_tiles) continue;
         const float tg = target[k], b = base[i], p0 = P[i];
         const float f = __builtin_amdgcn_exp2f((b - mx) * c);
-        const float4 ps = part[i];
         // (the sums that P is made of, so the part has a weight: behind one without, the next starts no later)
-        const int pi = __builtin_amdgcn_readfirstlane(fmaf(f, ps.z, p0) <= tg ? 3 : fmaf(f, ps.y, p0) <= tg ? 2 : fmaf(f, ps.x, p0) <= tg ? 1 : 0);
+        int pi = 0;
+#pragma unroll
+        for (int p = 1; p < PARTS; ++p)
+            if (fmaf(f, part[i][p - 1], p0) <= tg) pi = p;
+        pi = __builtin_amdgcn_readfirstlane(pi);
         const int a0 = i * kTile + pi * kPart;
         if (a0 != held) {
             held = a0;
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 4 ?
             const float incl = wave_scan(sum, lane);
             float excl = __shfl_up(incl, 1);
             if (lane == 0) excl = 0.f;
-            start = p0 + f * ((pi == 0 ? 0.f : pi == 1 ? ps.x : pi == 2 ? ps.y : ps.z) + excl);
+            start = p0 + f * ((pi == 0 ? 0.f : part[i][pi - 1]) + excl);
         }
         // (the scan's sums do not rise evenly: lanes behind the last weight may start at or below the target)
         const uint64_t below = weighted & __builtin_amdgcn_ballot_w64(start <= tg);
@@ -336,8 +340,7 @@ TKV_EXPORT int tkv_cd_sample(int32_t n_rows, int32_t vocab, float temperature, i
                              int32_t n_draws, int32_t* d_token, int32_t* d_count, int32_t* d_n_groups, void* stream) {
     tkv::clear_error();
     if (n_rows < 0 || vocab < 1) return tkv::set_error(TKV_EINVAL, "tkv_cd_sample: n_rows %d, vocab %d", n_rows, vocab);
-    if (vocab > kMaxTiles * kTile)
-        return tkv::set_error(TKV_EINVAL, "tkv_cd_sample: vocabulary %d exceeds %d", vocab, kMaxTiles * kTile);
+    if (vocab > kMaxVocab) return tkv::set_error(TKV_EINVAL, "tkv_cd_sample: vocabulary %d exceeds %d", vocab, kMaxVocab);
     if (!(temperature > 0.f) || !std::isfinite(temperature))
         return tkv::set_error(TKV_EINVAL, "tkv_cd_sample: temperature must be positive and finite");
     if (max_potential < 0 || max_potential > kMaxPotential)
@@ -356,17 +359,42 @@ TKV_EXPORT int tkv_cd_sample(int32_t n_rows, int32_t vocab, float temperature, i
     // 171 us on 1,627 rows of 151,936); smaller ones may still sit there, as the head's product left
     // them, and the hint would pass that by (19.2 against 15.2 us on 16 rows, 19.9 against 16.0 on 64).
     // Up to 256 rows each row has a CU to itself and takes 16 waves (15.4 against 18.4 us with 8 on 16
-    // rows of 151,936; the same below 16,384 tokens).  Beyond that several rows share a CU: 4 waves while
-    // each has at most four tiles (1,600 rows: 15.5 against 27.8 us at 600 tokens, 40.6 against 47.5 at
-    // 32,000), 8 on longer rows (171 against 175 us at 151,936).
-    if (static_cast<int64_t>(n_rows) * vocab > (int64_t{256} << 20) / 4)
-        launch(cd_sample<8, true, kMaxTiles>, 8);
-    else if (n_rows <= 256)
-        launch(cd_sample<16, false, kMaxTiles>, 16);
-    else if (vocab <= kShortTiles * kTile)
-        launch(cd_sample<4, false, kShortTiles>, 4);
-    else
-        launch(cd_sample<8, false, kMaxTiles>, 8);
+    // rows of 151,936).  Beyond that several rows share a CU, and waves without a tile of their own only
+    // hold up the next workgroup: 4 waves up to 65,536 logits (1,000 rows of 50,257 36.8 us, 38.2 with 8, 50.2
+    // with 16), 2 for more rows of up to 32,768 (5,000 rows of 17,000 63 us, 73 with 4, 110 with 8) while
+    // their draws are few, 8 on longer rows (171 against 175 us with 4 at 151,936) and past the cache from
+    // 32,768 on (1,600 rows of 50,257 58.8 us, 61.3 with 4).
+    // Rows of up to 16,384 logits take tiles of one part: 300 rows of 600 6.1 us, 8.3 with four parts;
+    // 20,000 rows of 4,000 69 us, 94; 120,000 rows of 600 353 us, 654; 256 rows of 8,191 on 16 waves 6.3 us,
+    // 6.9.  Many draws a row want more waves (1,000 rows of 4,096 with 200 draws: 116 us on 8, 128 on 4).
+    const bool past = static_cast<int64_t>(n_rows) * vocab > (int64_t{256} << 20) / 4;
+    if (vocab <= 16 * kPart) {
+        if (n_rows <= 256)
+            launch(cd_sample<16, 1, false, 16>, 16);
+        else if (max_potential > 64)
+            launch(cd_sample<8, 1, false, 16>, 8);
+        else if (past)
+            launch(cd_sample<4, 1, true, 16>, 4);
+        else
+            launch(cd_sample<4, 1, false, 16>, 4);
+    } else if (n_rows > 256 && vocab <= (past ? 8 : 16) * 4 * kPart) {
+        if (n_rows > 1024 && vocab <= 8 * 4 * kPart && max_potential <= 8) {
+            if (past)
+                launch(cd_sample<2, 4, true, 8>, 2);
+            else
+                launch(cd_sample<2, 4, false, 8>, 2);
+        } else if (past) {
+            launch(cd_sample<4, 4, true, 16>, 4);
+        } else {
+            launch(cd_sample<4, 4, false, 16>, 4);
+        }
+    } else if (past) {
+        launch(cd_sample<8, 4, true, 512>, 8);
+    } else if (n_rows <= 256) {
+        launch(cd_sample<16, 4, false, 512>, 16);
+    } else {
+        launch(cd_sample<8, 4, false, 512>, 8);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return tkv::set_error(TKV_EHIP, "tkv_cd_sample launch: %s", hipGetErrorString(e));
     return TKV_OK;

@@ -4,8 +4,8 @@ A draw is an integer decided by floating point: the oracle takes it on the exact
 kernel on its fp32 sums.  Where a uniform lies farther than delta from every boundary of the exact
 CDF the two must agree; within delta of a boundary any token in reach is a valid draw.  delta bounds
 the kernel's rounding relative to the total: a cumulative weight passes through at most 16 additions
-within a thread, 6 in the wave scan, 3 over the wave totals, a scaling and an addition per tile (n_tiles
-= vocab / 4096 tiles, each scaled once), so at most (31 + 2 n_tiles) roundings of 2^-24 of the total;
+within a thread, 6 in the wave scan, 3 over the parts, a scaling and an addition per tile (n_tiles
+= vocab / 4096 tiles, or vocab / 1024 up to 16,384 tokens, each scaled once), so at most (31 + 2 n_tiles) roundings of 2^-24 of the total;
 each weight also carries the error of exp2 and of its rounded argument (below 1e-6 of the total for
 these logits).  delta = 2 (31 + 2 n_tiles) 2^-24 + 1e-6 doubles the rounding part.  With 151,936 tokens
 of a flat distribution many tokens' probability intervals are narrower than delta; there the check is
@@ -22,7 +22,7 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 def _delta(vocab):
-    return 2 * (31 + 2 * math.ceil(vocab / 4096)) * 2.0 ** -24 + 1e-6
+    return 2 * (31 + 2 * math.ceil(vocab / (1024 if vocab <= 16384 else 4096))) * 2.0 ** -24 + 1e-6
 
 
 def _acceptable(logits, temperature, uniforms):
@@ -94,12 +94,16 @@ def test_cd_sample_matches_oracle(vocab, temperature, scale):
         assert all(np.isfinite(logits[r, t]) for t in toks)
 
 
+@pytest.mark.parametrize("max_potential", [64, 8, 65])
 @pytest.mark.parametrize("n_rows,vocab", [(256, 4096), (257, 8191), (300, 16 * 4096), (300, 16 * 4096 + 1),
-                                          (5, 3 * 4096 + 1), (460, 151939)])
-def test_cd_sample_workgroup_sizes(n_rows, vocab):
-    # 16 waves per row up to 256 rows, beyond them 4 (up to 16 tiles) or 8, non-temporal loads past 256 MB
-    # of logits (460 rows of 151,939); tiles that end with the vocabulary, one token into the next tile, and rows that do not
-    # start 16-byte aligned.  The first and last rows are checked against the oracle.
+                                          (5, 3 * 4096 + 1), (460, 151939), (256, 16384), (257, 16384), (257, 16385),
+                                          (256, 16385), (1024, 32768), (1025, 32768), (1025, 32769), (1500, 1025),
+                                          (300, 5), (8200, 8191), (4100, 16399), (2050, 32771)])
+def test_cd_sample_workgroup_sizes(n_rows, vocab, max_potential):
+    # 16 waves per row up to 256 rows, beyond them 2 (more than 1,024 rows of up to 32,768 tokens), 4 (up to 65,536)
+    # or 8; tiles of 1,024 logits up to 16,384 tokens, with 8 waves for many draws; non-temporal loads past 256 MB
+    # of logits.  Tiles that end with the vocabulary, one token into the next tile, and rows that do not start
+    # 16-byte aligned.  The first and last rows are checked against the oracle.
     g = torch.Generator(device="cuda")
     g.manual_seed(vocab)
     logits = torch.empty((n_rows, vocab), device="cuda").normal_(0.0, 4.0, generator=g)
@@ -107,11 +111,11 @@ def test_cd_sample_workgroup_sizes(n_rows, vocab):
     host = logits[rows].cpu().numpy()
     rng = np.random.default_rng(vocab)
     potential = rng.integers(0, 5, size=n_rows)
-    potential[rows] = [3, 64, 1, 17]
+    potential[rows] = [3, max_potential, 1, min(17, max_potential)]
     import paper_2609_39334_amd as tkv
     off = np.concatenate([[0], np.cumsum(potential)]).astype(np.int32)
     u = rng.random(int(off[-1]), dtype=np.float32)
-    tok, cnt, ng = tkv.tkv_cd_sample(logits, 0.8, torch.from_numpy(off).cuda(), torch.from_numpy(u).cuda(), 64)
+    tok, cnt, ng = tkv.tkv_cd_sample(logits, 0.8, torch.from_numpy(off).cuda(), torch.from_numpy(u).cuda(), max_potential)
     tok, cnt, ng = tok.cpu().numpy(), cnt.cpu().numpy(), ng.cpu().numpy()
     assert [int(sum(cnt[off[r]:off[r] + ng[r]])) for r in range(n_rows)] == potential.tolist()
     sub = np.concatenate([np.arange(off[r], off[r + 1]) for r in rows])
@@ -119,15 +123,15 @@ def test_cd_sample_workgroup_sizes(n_rows, vocab):
                 tok[sub], cnt[sub], ng[rows])
 
 
-@pytest.mark.parametrize("n_rows", [1, 300, 20000])
+@pytest.mark.parametrize("n_rows,vocab", [(1, 12293), (300, 12293), (20000, 12293), (1, 16389), (300, 16389), (1100, 16389),
+                                          (300, 65541)])
 @pytest.mark.parametrize("mask", [-3.4028234663852886e38, float("-inf"), -1e4])
-def test_cd_sample_never_draws_a_zero_weight(n_rows, mask):
+def test_cd_sample_never_draws_a_zero_weight(n_rows, vocab, mask):
     # Weights 1, 2^-24 and 2^-24 in the second to fourth lane of a part, everything else masked, and a target
     # of exactly 1 under a total of 1 + 2^-23: lanes behind the weights, whose sums are added in another order,
     # start at 1 as well.  c = 1 and whole logits, so that every weight is a power of two.  Then u = 1, past
-    # every tile, and draws over the whole range.  (16, 4 and 8 waves a row, the last with non-temporal loads.)
+    # every tile, and draws over the whole range.
     import paper_2609_39334_amd as tkv
-    vocab = 3 * 4096 + 5
     temperature = float(np.float32(1.4426950408889634))
     logits = torch.full((n_rows, vocab), mask, dtype=torch.float32, device="cuda")
     first = 4096 + 1024                       # the second part of the second tile
