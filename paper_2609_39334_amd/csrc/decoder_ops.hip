@@ -16,7 +16,7 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kHeldVecs = 8;  // float4s of a row that a thread of add_rmsnorm keeps: rows of up to 8,192
+constexpr int kHeldVecs = 8;  // float4s of a row that a thread of add_rmsnorm keeps
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -27,21 +27,28 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ float lo_f32(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float hi_f32(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
+template <int T>
 __device__ __forceinline__ float block_sum(float v, float* red) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < T / 64; k += 4) sum += (red[k] + red[k + 1]) + (red[k + 2] + red[k + 3]);
+    return sum;
 }
 
-// One workgroup per row.  Rows of up to 8,192 (a multiple of eight) stay in registers between the sum of
-// squares and the scaling; other rows are read again (from the caches: the thread has just written them).
-template <bool HELD>
-__global__ __launch_bounds__(kThreads) void add_rmsnorm(int hidden, float eps, float* __restrict__ x,
-                                                        const uint16_t* __restrict__ delta,
-                                                        const float* __restrict__ weight, uint16_t* __restrict__ h) {
-    __shared__ float red[kThreads / 64];
+// One workgroup of T threads per row.  Rows of up to 32 T (a multiple of eight) stay in registers between the
+// sum of squares and the scaling; other rows are read again (from the caches: the thread has just written
+// them).  256 threads up to 8,192, 512 up to 16,384 (one row of 16,384 23 us read again by 256, 8.7 us held;
+// 1,500 rows 67, 45); 1,024 for other rows of more than 4,096 (one row of 20,480 29 us with 256, 9.9 us;
+// 1,500 rows 84, 72).
+template <int T, bool HELD>
+__global__ __launch_bounds__(T) void add_rmsnorm(int hidden, float eps, float* __restrict__ x,
+                                                 const uint16_t* __restrict__ delta, const float* __restrict__ weight,
+                                                 uint16_t* __restrict__ h) {
+    __shared__ float red[T / 64];
     const size_t row = static_cast<size_t>(blockIdx.x) * hidden;
     const int t = threadIdx.x;
     float sq = 0.f;
@@ -52,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm(int hidden, float eps, f
         float4 v[kHeldVecs];
 #pragma unroll
         for (int k = 0; k < kHeldVecs; ++k) {
-            const int i = t + k * kThreads;
+            const int i = t + k * T;
             if (i >= n4) continue;
             v[k] = x4[i];
             if (delta) {
@@ -65,18 +72,18 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm(int hidden, float eps, f
             }
             sq += (v[k].x * v[k].x + v[k].y * v[k].y) + (v[k].z * v[k].z + v[k].w * v[k].w);
         }
-        const float r = 1.f / sqrtf(block_sum(sq, red) / static_cast<float>(hidden) + eps);
+        const float r = 1.f / sqrtf(block_sum<T>(sq, red) / static_cast<float>(hidden) + eps);
         const float4* w4 = reinterpret_cast<const float4*>(weight);
         uint2* h2 = reinterpret_cast<uint2*>(h + row);
 #pragma unroll
         for (int k = 0; k < kHeldVecs; ++k) {
-            const int i = t + k * kThreads;
+            const int i = t + k * T;
             if (i >= n4) continue;
             const float4 w = w4[i];
             h2[i] = uint2{pack_bf16x2(v[k].x * r * w.x, v[k].y * r * w.y), pack_bf16x2(v[k].z * r * w.z, v[k].w * r * w.w)};
         }
     } else {
-        for (int i = t; i < hidden; i += kThreads) {
+        for (int i = t; i < hidden; i += T) {
             float v = x[row + i];
             if (delta) {
                 v += lo_f32(delta[row + i]);
@@ -84,8 +91,8 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm(int hidden, float eps, f
             }
             sq += v * v;
         }
-        const float r = 1.f / sqrtf(block_sum(sq, red) / static_cast<float>(hidden) + eps);
-        for (int i = t; i < hidden; i += kThreads)
+        const float r = 1.f / sqrtf(block_sum<T>(sq, red) / static_cast<float>(hidden) + eps);
+        for (int i = t; i < hidden; i += T)
             h[row + i] = static_cast<uint16_t>(pack_bf16x2(x[row + i] * r * weight[i], 0.f));
     }
 }
@@ -192,11 +199,21 @@ TKV_EXPORT int tkv_add_rmsnorm(int32_t n_rows, int32_t hidden, float eps, float*
     if (n_rows < 0 || hidden < 1) return tkv::set_error(TKV_EINVAL, "tkv_add_rmsnorm: n_rows %d, hidden %d", n_rows, hidden);
     if (n_rows == 0) return TKV_OK;
     if (!x || !weight || !h) return tkv::set_error(TKV_EINVAL, "tkv_add_rmsnorm: NULL pointer");
-    const bool held = hidden % 8 == 0 && hidden <= 4 * kHeldVecs * kThreads && aligned16(x) && aligned16(delta) &&
+    const bool held = hidden % 8 == 0 && hidden <= 4 * kHeldVecs * 512 && aligned16(x) && aligned16(delta) &&
                       aligned16(weight) && aligned16(h);
-    const auto kernel = held ? add_rmsnorm<true> : add_rmsnorm<false>;
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_rows)), dim3(kThreads), 0, static_cast<hipStream_t>(stream),
-                       hidden, eps, x, static_cast<const uint16_t*>(delta), weight, static_cast<uint16_t*>(h));
+    const auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_rows)), dim3(static_cast<unsigned>(threads)), 0,
+                           static_cast<hipStream_t>(stream), hidden, eps, x, static_cast<const uint16_t*>(delta), weight,
+                           static_cast<uint16_t*>(h));
+    };
+    if (held && hidden <= 4 * kHeldVecs * 256)
+        launch(add_rmsnorm<256, true>, 256);
+    else if (held)
+        launch(add_rmsnorm<512, true>, 512);
+    else if (hidden <= 4096)
+        launch(add_rmsnorm<256, false>, 256);
+    else
+        launch(add_rmsnorm<1024, false>, 1024);
     return launched("tkv_add_rmsnorm");
 }
 

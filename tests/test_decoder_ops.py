@@ -28,10 +28,11 @@ def _randn(g, *shape):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows,hidden", [(1, 8), (3, 1024), (5, 3584), (2, 8192), (2, 8200), (7, 1001), (4, 12)])
+@pytest.mark.parametrize("rows,hidden", [(1, 8), (3, 1024), (5, 3584), (2, 8192), (2, 8200), (7, 1001), (4, 12), (2, 16384),
+                                         (2, 16392), (3, 4095), (3, 4097), (1, 30001)])
 @pytest.mark.parametrize("with_delta", [False, True])
 def test_add_rmsnorm(rows, hidden, with_delta):
-    # rows held in registers (multiples of 8 up to 8,192) and read again (longer, odd)
+    # rows held in registers (multiples of 8 up to 8,192, and to 16,384) and read again (longer, odd)
     g = _gen(hidden)
     x, w = _randn(g, rows, hidden) * 3, torch.rand(hidden, generator=g, device="cuda") + 0.5
     delta = _randn(g, rows, hidden).bfloat16() if with_delta else None
