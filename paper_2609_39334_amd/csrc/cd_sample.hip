@@ -365,7 +365,7 @@ TKV_EXPORT int tkv_cd_sample(int32_t n_rows, int32_t vocab, float temperature, i
     // their draws are few, 8 on longer rows (171 against 175 us with 4 at 151,936) and past the cache from
     // 32,768 on (1,600 rows of 50,257 58.8 us, 61.3 with 4).
     // Rows of up to 16,384 logits take tiles of one part: 300 rows of 600 6.1 us, 8.3 with four parts;
-    // 20,000 rows of 4,000 69 us, 94; 120,000 rows of 600 353 us, 654; 256 rows of 8,191 on 16 waves 6.3 us,
+    // 20,000 rows of 4,096 70 us, 94; 120,000 rows of 600 353 us, 654; 256 rows of 8,191 on 16 waves 6.3 us,
     // 6.9.  Many draws a row want more waves (1,000 rows of 4,096 with 200 draws: 116 us on 8, 128 on 4).
     const bool past = static_cast<int64_t>(n_rows) * vocab > (int64_t{256} << 20) / 4;
     if (vocab <= 16 * kPart) {
